@@ -61,9 +61,18 @@ int bucket_of(int L) {
 
 inline int pad8(int n) { return (n + 7) / 8 * 8; }
 
-__global__ void zero_u64_n(unsigned long long* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0ull;
+__global__ __launch_bounds__(NORM_WORDS) void batch_norms_zero(unsigned long long* slots) {
+  slots[(size_t)blockIdx.x * NORM_WORDS + threadIdx.x] = 0ull;
+}
+
+// The slots of solve blockIdx.x -> out[2 blockIdx.x], out[2 blockIdx.x + 1].
+__global__ __launch_bounds__(64) void batch_norms_max(const unsigned long long* __restrict__ slots,
+                                                      unsigned long long* __restrict__ out) {
+  const int v = threadIdx.x & 1, q = threadIdx.x >> 1;
+  static_assert(NORM_SLOTS == 32, "one slot per lane pair");
+  unsigned long long m = slots[(size_t)blockIdx.x * NORM_WORDS + q * NORM_STRIDE + v];
+  for (int s = 32; s >= 2; s >>= 1) m = max(m, (unsigned long long)__shfl_xor((long long)m, s));
+  if (threadIdx.x < 2) out[2 * (size_t)blockIdx.x + v] = m;
 }
 
 struct Group {
@@ -93,7 +102,7 @@ struct sem_batch {
   LpDesc* d_desc = nullptr;
   ResDesc* d_rdesc = nullptr;
   int* d_active = nullptr;
-  unsigned long long* d_norms = nullptr;
+  unsigned long long* d_norms = nullptr;  // norm slots of the solves, then 2 maxima per solve
   std::vector<LpDesc> h_desc;
   std::vector<ResDesc> h_rdesc;
   std::vector<Group> groups;
@@ -159,7 +168,7 @@ LpDesc make_desc(sem_batch* b, int i, int v, const double* f, double* u) {
   }
   if (s == 5) {
     d.epi.first = v == 6 ? 1 : 0;
-    d.epi.norms = b->d_norms + 2 * i;
+    d.epi.norms = b->d_norms + (size_t)NORM_WORDS * i;
   }
   return d;
 }
@@ -376,7 +385,7 @@ hipError_t split_iteration(sem_batch* b, int i, int it, const double* f, double*
     e = launch_residual(ra, hb, p->k, p->dims, stream);
   }
   if (e == hipSuccess)
-    e = lp_fd(p, w, Spectral{p->alpha, 1.0, 0.0}, it == 0 ? f : nullptr, u, it == 0 ? 1 : 0, b->d_norms + 2 * i);
+    e = lp_fd(p, w, Spectral{p->alpha, 1.0, 0.0}, it == 0 ? f : nullptr, u, it == 0 ? 1 : 0, b->d_norms + (size_t)NORM_WORDS * i);
   p->stream = keep;
   return e;
 }
@@ -453,7 +462,7 @@ sem_status sem_batch_create(int count, sem_plan* const* plans, sem_batch** out) 
   if ((e = hipMalloc(&b->d_desc, sizeof(LpDesc) * (size_t)std::max(NVAR * count, 3 * count))) != hipSuccess ||
       (e = hipMalloc(&b->d_rdesc, sizeof(ResDesc) * (size_t)count)) != hipSuccess ||
       (e = hipMalloc(&b->d_active, sizeof(int) * (size_t)count)) != hipSuccess ||
-      (e = hipMalloc(&b->d_norms, 2 * sizeof(unsigned long long) * (size_t)count)) != hipSuccess) {
+      (e = hipMalloc(&b->d_norms, (NORM_WORDS + 2) * sizeof(unsigned long long) * (size_t)count)) != hipSuccess) {
     sem_batch_destroy(b);
     return hip_fail(e, "sem_batch_create: device allocation");
   }
@@ -555,7 +564,7 @@ sem_status sem_batch_solve(sem_batch* b, sem_prec prec, double tol, int max_iter
     if ((e = hipMemcpyAsync(b->d_active, dev_active.data(), n * sizeof(int), hipMemcpyHostToDevice, b->stream)) !=
         hipSuccess)
       return hip_fail(e, "sem_batch_solve: active flags");
-    zero_u64_n<<<(2 * n + 255) / 256, 256, 0, b->stream>>>(b->d_norms, 2 * n);
+    batch_norms_zero<<<n, NORM_WORDS, 0, b->stream>>>(b->d_norms);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "sem_batch_solve: norm reset");
     // split solves on the side streams, after the norm reset and concurrently with
     // the persistent launches below
@@ -595,7 +604,10 @@ sem_status sem_batch_solve(sem_batch* b, sem_prec prec, double tol, int max_iter
       drain();
       return hip_fail(e, "sem_batch_solve: event");
     }
-    if ((e = hipMemcpyAsync(hn.data(), b->d_norms, hn.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost,
+    unsigned long long* const maxima = b->d_norms + (size_t)NORM_WORDS * n;
+    batch_norms_max<<<n, 64, 0, b->stream>>>(b->d_norms, maxima);
+    if ((e = hipGetLastError()) != hipSuccess ||
+        (e = hipMemcpyAsync(hn.data(), maxima, hn.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost,
                             b->stream)) != hipSuccess ||
         (e = hipStreamSynchronize(b->stream)) != hipSuccess) {
       drain();

@@ -73,10 +73,23 @@ hipError_t launch_fold_f64(const double* x, double* y, long P, int n, long Q, in
 // ---- low-precision rotating mode products (mode_lp.hip) ----
 enum { LP_F32 = 1, LP_BF16 = 2, LP_BF16X3 = 3 };
 
+// Update norms max|delta|, max|u| of the refinement, kept as FP64 bit patterns
+// (non-negative doubles order like their unsigned bits).  Blocks spread their
+// atomic maxima over NORM_SLOTS slots of one 128-byte line each: with one slot for
+// all, the atomics of a launch (device scope, past the XCDs' L2s) queue up at about
+// 12 ns each, which was 89 of the 89 us of the unfold at n = 119 (3600 blocks) and
+// 60 of the 82 us of the last FP32 pass at (127, 163, 143).
+constexpr int NORM_SLOTS = 32, NORM_STRIDE = 16;       // stride in 8-byte words
+constexpr int NORM_WORDS = NORM_SLOTS * NORM_STRIDE;  // words per solve
+__device__ inline void norm_max(unsigned long long* norms, double dmax, double umax) {
+  unsigned long long* s = norms + (blockIdx.x % NORM_SLOTS) * NORM_STRIDE;
+  atomicMax(s, (unsigned long long)__double_as_longlong(dmax));
+  atomicMax(s + 1, (unsigned long long)__double_as_longlong(umax));
+}
+
 // Epilogue arguments: divide by alpha + b1 L + b2 L^2 with L = l0[l] + l1[a] +
 // l2[b] (third forward pass), or accumulate into FP64 (first = 1: u = delta)
-// recording norms[0] = max|delta|, norms[1] = max|u| (bit patterns, atomic max;
-// skipped when norms is null).
+// recording max|delta| and max|u| in the slots of norms (skipped when null).
 struct EpiLP {
   const double* l0 = nullptr;
   const double* l1 = nullptr;

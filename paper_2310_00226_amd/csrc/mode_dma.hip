@@ -650,7 +650,7 @@ __global__ __launch_bounds__(256) void fold_lowp_kernel(const unsigned short* __
 // with r its orbit representative and s = +1 (i = r) or -1 (i = R(r)).  A thread
 // owns one orbit {x, R(x)} x {y, R(y)} x {z, R(z)}: it reads the 8 values of the
 // orbit once and writes its (up to 8) nodes.  first = 1: u = correction.  norms
-// (may be null): atomic max of |delta| and |u| as FP64 bit patterns.
+// (may be null): slots of max|delta| and max|u| (norm_max).
 struct UnfoldAxis {
   int n, nrep, per;
 };
@@ -758,8 +758,7 @@ __global__ __launch_bounds__(NT) void unfold_accum_kernel(const float* __restric
         dmax = fmax(dmax, red[0][w]);
         umax = fmax(umax, red[1][w]);
       }
-      atomicMax(norms, (unsigned long long)__double_as_longlong(dmax));
-      atomicMax(norms + 1, (unsigned long long)__double_as_longlong(umax));
+      norm_max(norms, dmax, umax);
     }
   }
 }

@@ -241,17 +241,25 @@ __device__ __forceinline__ void tile_body(const LpDesc& d, long t, float* __rest
     }
   if constexpr (EPI == EPI_ACCUM) {
     if (epi.norms) {
-      // wave max, then one atomic per wave on the bit pattern (non-negative
-      // doubles order like their unsigned integer bits)
+      // wave maxima, then one atomic pair per block
 #pragma unroll
       for (int s = 32; s >= 1; s >>= 1) {
         dmax = fmax(dmax, __shfl_xor(dmax, s));
         umax = fmax(umax, __shfl_xor(umax, s));
       }
+      double* red = reinterpret_cast<double*>(lds);
+      __syncthreads();  // every wave is done with the operand tiles
       if (lane == 0) {
-        atomicMax(reinterpret_cast<unsigned long long*>(epi.norms), (unsigned long long)__double_as_longlong(dmax));
-        atomicMax(reinterpret_cast<unsigned long long*>(epi.norms) + 1,
-                  (unsigned long long)__double_as_longlong(umax));
+        red[2 * wave] = dmax;
+        red[2 * wave + 1] = umax;
+      }
+      __syncthreads();
+      if (tid == 0) {
+        for (int w = 1; w < NTHREADS / 64; ++w) {
+          dmax = fmax(dmax, red[2 * w]);
+          umax = fmax(umax, red[2 * w + 1]);
+        }
+        norm_max(epi.norms, dmax, umax);
       }
     }
   }

@@ -78,7 +78,7 @@ struct LpWork {
   void* r = nullptr;        // residual / right-hand side in the intermediate format
   void* t0 = nullptr;       // rotating intermediates
   void* t1 = nullptr;
-  unsigned long long* norms = nullptr;  // 2 x FP64 bit patterns
+  unsigned long long* norms = nullptr;  // NORM_WORDS words (norm_max)
   int rkind = 1, ldr = 0;   // ResidualArgs.r_kind and row pitch of r
   long rplane = 0, tplane = 0;
   // BF16 modes: t1 already holds the folded input of the first pass (written by

@@ -97,9 +97,7 @@ size_t lp_r_bytes(const sem_plan* p, sem_prec prec) {
   return ((lp_r_elems(p, prec) * lp_elem(prec) + 255) / 256) * 256;
 }
 
-__global__ void zero_u64_kernel(unsigned long long* p, int n) {
-  if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
-}
+__global__ void zero_norms_kernel(unsigned long long* p) { p[threadIdx.x] = 0ull; }
 
 }  // namespace
 
@@ -113,7 +111,7 @@ size_t workspace_need(const sem_plan* p, sem_prec prec) {
     case SEM_BF16X3: {
       const size_t r = lp_r_bytes(p, prec);
       const size_t t = ((lp_tmp_elems(p, prec) * lp_elem(prec) + 255) / 256) * 256;
-      return r + 2 * t + 256;
+      return r + 2 * t + NORM_WORDS * sizeof(unsigned long long);
     }
     default:
       return 0;
@@ -446,8 +444,8 @@ static LpPass f32_pass(sem_plan* p, const LpWork& w, const Spectral& sp, int s, 
 //    directly; the BF16 modes fold and convert it first);
 //  f64_src == null: src is w.r, written by the residual kernel in the
 //    intermediate format (row pitch w.ldr).
-//  first = 1 stores u = delta, else u += delta; norms (may be null) receive
-//  max|delta| and max|u| as FP64 bit patterns (the caller zeroes them).
+//  first = 1 stores u = delta, else u += delta; the slots of norms (may be null)
+//  receive max|delta| and max|u| (the caller zeroes them).
 hipError_t lp_fd(sem_plan* p, const LpWork& w, const Spectral& sp, const double* f64_src, double* u, int first,
                  unsigned long long* norms) {
   if (w.prec != SEM_F32) return lp_fd_folded(p, w, sp, f64_src, u, first, norms);
@@ -644,7 +642,7 @@ hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, dou
 }
 
 hipError_t zero_norms(unsigned long long* norms, hipStream_t stream) {
-  zero_u64_kernel<<<1, 64, 0, stream>>>(norms, 2);
+  zero_norms_kernel<<<1, NORM_WORDS, 0, stream>>>(norms);
   return hipGetLastError();
 }
 
@@ -692,10 +690,12 @@ extern "C" sem_status sem_solve_refined(sem_plan* p, sem_prec prec, double tol, 
     if ((e = zero_norms(w.norms, p->stream)) != hipSuccess) return hip_fail(e, "sem_solve_refined: norm reset");
     if ((e = lp_fd(p, w, sp, it == 0 ? f : nullptr, u, it == 0 ? 1 : 0, w.norms)) != hipSuccess)
       return hip_fail(e, "sem_solve_refined: low-precision solve");
-    unsigned long long hn[2];
+    unsigned long long hn[NORM_WORDS];
     if ((e = hipMemcpyAsync(hn, w.norms, sizeof(hn), hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
         (e = hipStreamSynchronize(p->stream)) != hipSuccess)
       return hip_fail(e, "sem_solve_refined: norm readback");
+    for (int q = 1; q < NORM_SLOTS; ++q)
+      for (int v = 0; v < 2; ++v) hn[v] = std::max(hn[v], hn[q * NORM_STRIDE + v]);
     double dmax, umax;
     std::memcpy(&dmax, &hn[0], 8);
     std::memcpy(&umax, &hn[1], 8);
