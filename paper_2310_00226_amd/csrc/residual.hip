@@ -368,12 +368,19 @@ __global__ __launch_bounds__(RT) void residual_march_batch(const ResDesc* __rest
 }
 
 // x is split into chunks so that the grid fills the chip even for thin (y, z)
-// planes; a chunk spans at least 8 k planes, since each chunk first loads the 2k
-// planes of its window
+// planes.  A chunk spans at least 8 k planes, since each chunk first loads the 2k
+// planes of its window, unless that leaves fewer than two blocks per CU: a plane
+// of the march is a serial step of about 1 us, so short chunks with the window
+// loads overlapped win there.  FP64 residual, 8 k planes against this rule: k = 5,
+// 119^3 (16 columns of blocks) 77.8 -> 23.6 us; k = 8, (191, 199, 119) 167 -> 89;
+// k = 4, 31^3 44 -> 9.2; (127, 163, 143) 55 -> 35.  With 1024 blocks as the line
+// k = 4, 255^3 takes 129 instead of 116 us, with 256 k = 8 takes 104.
+constexpr int MARCH_BLOCKS = 512;
 void march_grid(const int dims[3], int k, int* gx, int* gy, int* gz, int* xchunk) {
   const long cols = (long)((dims[2] + RZ - 1) / RZ) * ((dims[1] + RY - 1) / RY);
   int nchunks = (int)std::min<long>(dims[0], std::max<long>(1, (8192 + cols - 1) / cols));
-  *xchunk = std::max((dims[0] + nchunks - 1) / nchunks, std::min(dims[0], 8 * k));
+  const int least = (int)std::min<long>(8L * k, std::max<long>(2, dims[0] * cols / MARCH_BLOCKS));
+  *xchunk = std::max((dims[0] + nchunks - 1) / nchunks, std::min(dims[0], least));
   *gx = (dims[2] + RZ - 1) / RZ;
   *gy = (dims[1] + RY - 1) / RY;
   *gz = (dims[0] + *xchunk - 1) / *xchunk;
