@@ -70,6 +70,53 @@ hipError_t launch_mode_f64_part(const double* x, double* y, const double* g, int
 // (off = 1 periodic, 0 otherwise): Y has n rows like X.
 hipError_t launch_fold_f64(const double* x, double* y, long P, int n, long Q, int nrep, int per, hipStream_t stream);
 
+// ---- reflection-split products on strips in LDS (mode_strip.hip) ----
+// One axis of n nodes: nrep orbit representatives (and symmetric modes), nodd =
+// n - nrep antisymmetric modes, reflection n - 1 - r or, per, (n - r) mod n.
+struct StripAxis {
+  int n = 0, nrep = 0, nodd = 0, per = 0;
+};
+enum { STRIP_FWD = 0, STRIP_BWD = 1, STRIP_MUL = 2 };
+// Factors G[m][l] of pitch ldg (>= nrep rounded up to 16) with 17 zero rows behind
+// the contraction: fs, fa forward symmetric / antisymmetric (modes x representatives),
+// bs, ba backward (representatives x modes of the block).  Modes are in folded order.
+struct StripArgs {
+  const void* x = nullptr;
+  void* y = nullptr;  // may be x where their types and pitches agree
+  const void *fs = nullptr, *fa = nullptr, *bs = nullptr, *ba = nullptr;
+  int ldg = 0;
+  // planes: the y axis (ay) and its factors; ax and the factors above are the z axis
+  const void *fs2 = nullptr, *fa2 = nullptr, *bs2 = nullptr, *ba2 = nullptr;
+  int ldg2 = 0;
+  StripAxis ax, ay;
+  // columns: X[p][m][q], p < P, q < Q; rows: P rows of pitch ldx; planes: P planes
+  // of ay.n rows of pitch ldx
+  long P = 0, Q = 0;
+  int ldx = 0;
+  EpiArgs epi;  // STRIP_MUL (x axis, P = 1): multiplier with the folded eigenvalues
+  // FP32 rows / planes backward: u += product (first: u = product), norm slots or null
+  int first = 1;
+  unsigned long long* norms = nullptr;
+  // set by the launchers
+  int stride = 0, stride2 = 0;
+  long ntiles = 0;
+};
+constexpr long STRIP_MAX_Q = 1L << 22;  // 32-bit offsets of 64 rows inside a strip's base
+// Whether the strips take an axis / a pair of axes with elements of `elem` bytes.
+bool strip_axis_ok(const StripAxis& a, int elem);
+bool strip_plane_ok(const StripAxis& ay, const StripAxis& az, int elem);
+// y and x products: op STRIP_FWD, STRIP_BWD, or STRIP_MUL (forward, multiplier,
+// backward).  T = double or float.
+template <class T>
+hipError_t launch_strip_col(const StripArgs& g, int op, hipStream_t s);
+// z products: STRIP_FWD from TI rows of pitch ldx to T rows of n; STRIP_BWD from T
+// rows of n to FP64 nodes (T = float: accumulated).
+template <class T, class TI>
+hipError_t launch_strip_row(const StripArgs& g, int op, hipStream_t s);
+// z and y products of whole planes, as launch_strip_row followed / preceded by y.
+template <class T, class TI>
+hipError_t launch_strip_plane(StripArgs g, int op, hipStream_t s);
+
 // ---- low-precision rotating mode products (mode_lp.hip) ----
 enum { LP_F32 = 1, LP_BF16 = 2, LP_BF16X3 = 3 };
 

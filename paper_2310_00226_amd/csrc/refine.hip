@@ -549,45 +549,47 @@ sem_status lp_tune(sem_plan* p, const LpWork& w) {
   return SEM_OK;
 }
 
+static StripAxis strip_axis(const sem_plan* p, int a) {
+  return StripAxis{p->dims[a], p->ax[a].nrep, p->ax[a].nodd, p->bc[a] == SEM_BC_PERIODIC ? 1 : 0};
+}
+
 // FP64 FD application on the reflection-split transforms (the plan's folded
-// blocks), two launches per mode product.  The antisymmetric blocks use only the
-// nodd representatives that are not their own reflection (r = j + off, off = 1
-// on periodic axes, whose node 0 is fixed; the fixed node of an odd
-// non-periodic axis is the last representative), whose v- is not identically 0:
+// blocks).  Every product writes its modes in folded order ([symmetric |
+// antisymmetric]), so the multiplier reads the folded eigenvalues.
+// An axis that fits the strips of mode_strip.hip takes them: one launch per
+// product, forward, multiplier and backward of x in one launch, z and y in one
+// launch when the whole (y, z) plane fits.  Longer axes take the tiles of
+// mode_f64.hip, two launches per product.  There the antisymmetric blocks use only
+// the nodd representatives that are not their own reflection (r = j + off, off = 1
+// on periodic axes, whose node 0 is fixed; the fixed node of an odd non-periodic
+// axis is the last representative), whose v- is not identically 0:
 //  - z forward: the blocks read the unfolded z rows as v+ = x_r + x_R(r) or
 //    v- = x_r - x_R(r) in their loads;
 //  - y and x forward: a compact fold pass ([v+ of the nrep representatives |
 //    v- of the nodd others], n rows) feeds plain block products;
-//  - the forward blocks write the modes in folded order ([symmetric |
-//    antisymmetric]), so the x product's multiplier reads the folded eigenvalues;
 //  - backward (x, y, z): the symmetric block stores e_r at node r, the
 //    antisymmetric block reads it back and stores u_r = e_r + o_r and
 //    u_R(r) = e_r - o_r (at a fixed node e_r stays).
-// Buffers: f -> tmp -> u -> tmp -> u -> tmp -> u -> tmp -> u (tmp: N doubles; u
-// may alias f, which the first product alone reads).
+// Strip products run in place in tmp (N doubles); tile products go from one of tmp
+// and u to the other.  u may alias f, which the first product alone reads.
 hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, double* tmp) {
   const int nx = p->dims[0], ny = p->dims[1], nz = p->dims[2];
   const int r[3] = {p->ax[0].nrep, p->ax[1].nrep, p->ax[2].nrep};
   const int o[3] = {p->ax[0].nodd, p->ax[1].nodd, p->ax[2].nodd};
-  const int n[3] = {nx, ny, nz};
-  int per[3], off[3];
-  for (int a = 0; a < 3; ++a) {
-    per[a] = p->bc[a] == SEM_BC_PERIODIC ? 1 : 0;
-    off[a] = per[a];
-  }
   const long PZ = (long)nx * ny, QY = nz, PY = nx, QX = (long)ny * nz;
-  EpiArgs none;
-  EpiArgs plus_z, minus_z, unfold[3];
+  StripAxis ax[3];
+  bool strip[3];
+  EpiArgs none, plus_z, minus_z, unfold[3];
+  for (int a = 0; a < 3; ++a) {
+    ax[a] = strip_axis(p, a);
+    strip[a] = strip_axis_ok(ax[a], sizeof(double)) && (a > 0 || QX <= STRIP_MAX_Q);
+    unfold[a].rn = ax[a].n;
+    unfold[a].rper = unfold[a].roff = ax[a].per;
+  }
   plus_z.fold = 1;
   minus_z.fold = 2;
   plus_z.rn = minus_z.rn = nz;
-  plus_z.rper = minus_z.rper = per[2];
-  minus_z.roff = off[2];
-  for (int a = 0; a < 3; ++a) {
-    unfold[a].rn = n[a];
-    unfold[a].rper = per[a];
-    unfold[a].roff = off[a];
-  }
+  plus_z.rper = minus_z.rper = minus_z.roff = ax[2].per;
   EpiArgs mul;
   mul.lx = p->d_lamf64[0];
   mul.ly = p->d_lamf64[1];
@@ -601,42 +603,98 @@ hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, dou
   EpiArgs mul_anti = mul;
   mul_anti.lx = p->d_lamf64[0] + r[0];
   const int epi = sp.kind ? EPI_SPECTRAL : EPI_DIVIDE;
-  // antisymmetric blocks: forward factors start at row off (representative
-  // off), backward factors at column off
+  // antisymmetric blocks of the tiles: forward factors start at row off
+  // (representative off), backward factors at column off
   const double* gfa[3];
   const double* gba[3];
   for (int a = 0; a < 3; ++a) {
-    gfa[a] = p->d_gff[a][1] + (size_t)off[a] * p->fld[a];
-    gba[a] = p->d_gbf[a][1] + off[a];
+    gfa[a] = p->d_gff[a][1] + (size_t)ax[a].per * p->fld[a];
+    gba[a] = p->d_gbf[a][1] + ax[a].per;
   }
   hipStream_t s = p->stream;
   hipError_t e;
 #define SEMFD_TRY(x) \
   if ((e = (x)) != hipSuccess) return e
-  // z forward (NT shape, rows (x, y)), folding in the loads: f -> tmp (z modes)
-  SEMFD_TRY(launch_mode_f64_part(f, tmp, p->d_gff[2][0], p->fld[2], PZ, r[2], r[2], 1, nz, nz, EPI_STORE, plus_z, s));
-  SEMFD_TRY(launch_mode_f64_part(f, tmp + r[2], gfa[2], p->fld[2], PZ, o[2], o[2], 1, nz, nz, EPI_STORE, minus_z, s));
-  // y: fold tmp -> u, forward (batched over x, inner z modes) u -> tmp
-  SEMFD_TRY(launch_fold_f64(tmp, u, PY, ny, QY, r[1], per[1], s));
-  SEMFD_TRY(launch_mode_f64_part(u, tmp, p->d_gff[1][0], p->fld[1], PY, r[1], r[1], QY, ny, ny, EPI_STORE, none, s));
-  SEMFD_TRY(launch_mode_f64_part(u + (size_t)r[1] * QY, tmp + (size_t)r[1] * QY, gfa[1], p->fld[1], PY, o[1], o[1], QY,
-                                 ny, ny, EPI_STORE, none, s));
-  // x: fold tmp -> u, forward with the multiplier u -> tmp
-  SEMFD_TRY(launch_fold_f64(tmp, u, 1, nx, QX, r[0], per[0], s));
-  SEMFD_TRY(launch_mode_f64_part(u, tmp, p->d_gff[0][0], p->fld[0], 1, r[0], r[0], QX, nx, nx, epi, mul, s));
-  SEMFD_TRY(launch_mode_f64_part(u + (size_t)r[0] * QX, tmp + (size_t)r[0] * QX, gfa[0], p->fld[0], 1, o[0], o[0], QX,
-                                 nx, nx, epi, mul_anti, s));
-  // x backward: tmp (x modes) -> u (x nodes)
-  SEMFD_TRY(launch_mode_f64_part(tmp, u, p->d_gbf[0][0], p->fld[0], 1, r[0], r[0], QX, nx, nx, EPI_STORE, none, s));
-  SEMFD_TRY(launch_mode_f64_part(tmp + (size_t)r[0] * QX, u, gba[0], p->fld[0], 1, o[0], o[0], QX, nx, nx, EPI_UNFOLD,
-                                 unfold[0], s));
-  // y backward: u -> tmp
-  SEMFD_TRY(launch_mode_f64_part(u, tmp, p->d_gbf[1][0], p->fld[1], PY, r[1], r[1], QY, ny, ny, EPI_STORE, none, s));
-  SEMFD_TRY(launch_mode_f64_part(u + (size_t)r[1] * QY, tmp, gba[1], p->fld[1], PY, o[1], o[1], QY, ny, ny, EPI_UNFOLD,
-                                 unfold[1], s));
-  // z backward: tmp -> u
-  SEMFD_TRY(launch_mode_f64_part(tmp, u, p->d_gbf[2][0], p->fld[2], PZ, r[2], r[2], 1, nz, nz, EPI_STORE, none, s));
-  SEMFD_TRY(launch_mode_f64_part(tmp + r[2], u, gba[2], p->fld[2], PZ, o[2], o[2], 1, nz, nz, EPI_UNFOLD, unfold[2], s));
+  auto strip_args = [&](int a, const double* x, double* y, long P, long Q) {
+    StripArgs g;
+    g.x = x;
+    g.y = y;
+    g.fs = p->d_gff[a][0];
+    g.fa = p->d_gff[a][1];
+    g.bs = p->d_gbf[a][0];
+    g.ba = p->d_gbf[a][1];
+    g.ldg = p->fld[a];
+    g.ax = ax[a];
+    g.P = P;
+    g.Q = Q;
+    g.ldx = nz;
+    g.epi = mul;
+    return g;
+  };
+  const bool plane = strip_plane_ok(ax[1], ax[2], sizeof(double));
+  auto plane_args = [&](const double* x, double* y) {
+    StripArgs g = strip_args(2, x, y, nx, 1);
+    g.ay = ax[1];
+    g.fs2 = p->d_gff[1][0];
+    g.fa2 = p->d_gff[1][1];
+    g.bs2 = p->d_gbf[1][0];
+    g.ba2 = p->d_gbf[1][1];
+    g.ldg2 = p->fld[1];
+    return g;
+  };
+  if (plane) {  // z and y forward: f -> tmp
+    SEMFD_TRY((launch_strip_plane<double, double>(plane_args(f, tmp), STRIP_FWD, s)));
+  } else {
+    if (strip[2]) {
+      SEMFD_TRY((launch_strip_row<double, double>(strip_args(2, f, tmp, PZ, 1), STRIP_FWD, s)));
+    } else {  // z forward (NT shape, rows (x, y)), folding in the loads: f -> tmp (z modes)
+      SEMFD_TRY(launch_mode_f64_part(f, tmp, p->d_gff[2][0], p->fld[2], PZ, r[2], r[2], 1, nz, nz, EPI_STORE, plus_z,
+                                     s));
+      SEMFD_TRY(launch_mode_f64_part(f, tmp + r[2], gfa[2], p->fld[2], PZ, o[2], o[2], 1, nz, nz, EPI_STORE, minus_z,
+                                     s));
+    }
+    if (strip[1]) {
+      SEMFD_TRY(launch_strip_col<double>(strip_args(1, tmp, tmp, PY, QY), STRIP_FWD, s));
+    } else {  // y: fold tmp -> u, forward (batched over x, inner z modes) u -> tmp
+      SEMFD_TRY(launch_fold_f64(tmp, u, PY, ny, QY, r[1], ax[1].per, s));
+      SEMFD_TRY(launch_mode_f64_part(u, tmp, p->d_gff[1][0], p->fld[1], PY, r[1], r[1], QY, ny, ny, EPI_STORE, none,
+                                     s));
+      SEMFD_TRY(launch_mode_f64_part(u + (size_t)r[1] * QY, tmp + (size_t)r[1] * QY, gfa[1], p->fld[1], PY, o[1],
+                                     o[1], QY, ny, ny, EPI_STORE, none, s));
+    }
+  }
+  // x forward, multiplier, backward: the nodes along x land where the y product
+  // reads them (a tile product ends in u, a strip product in tmp)
+  double* cur = strip[1] && strip[0] ? tmp : u;
+  if (strip[0]) {
+    SEMFD_TRY(launch_strip_col<double>(strip_args(0, tmp, cur, 1, QX), STRIP_MUL, s));
+  } else {  // fold tmp -> u, forward with the multiplier u -> tmp, backward tmp -> u
+    SEMFD_TRY(launch_fold_f64(tmp, u, 1, nx, QX, r[0], ax[0].per, s));
+    SEMFD_TRY(launch_mode_f64_part(u, tmp, p->d_gff[0][0], p->fld[0], 1, r[0], r[0], QX, nx, nx, epi, mul, s));
+    SEMFD_TRY(launch_mode_f64_part(u + (size_t)r[0] * QX, tmp + (size_t)r[0] * QX, gfa[0], p->fld[0], 1, o[0], o[0],
+                                   QX, nx, nx, epi, mul_anti, s));
+    SEMFD_TRY(launch_mode_f64_part(tmp, u, p->d_gbf[0][0], p->fld[0], 1, r[0], r[0], QX, nx, nx, EPI_STORE, none, s));
+    SEMFD_TRY(launch_mode_f64_part(tmp + (size_t)r[0] * QX, u, gba[0], p->fld[0], 1, o[0], o[0], QX, nx, nx,
+                                   EPI_UNFOLD, unfold[0], s));
+  }
+  if (plane) {  // y and z backward: cur -> u (a plane is read before it is written)
+    SEMFD_TRY((launch_strip_plane<double, double>(plane_args(cur, u), STRIP_BWD, s)));
+    return hipSuccess;
+  }
+  if (strip[1]) {
+    SEMFD_TRY(launch_strip_col<double>(strip_args(1, cur, tmp, PY, QY), STRIP_BWD, s));
+  } else {  // y backward: u -> tmp
+    SEMFD_TRY(launch_mode_f64_part(u, tmp, p->d_gbf[1][0], p->fld[1], PY, r[1], r[1], QY, ny, ny, EPI_STORE, none, s));
+    SEMFD_TRY(launch_mode_f64_part(u + (size_t)r[1] * QY, tmp, gba[1], p->fld[1], PY, o[1], o[1], QY, ny, ny,
+                                   EPI_UNFOLD, unfold[1], s));
+  }
+  if (strip[2]) {
+    SEMFD_TRY((launch_strip_row<double, double>(strip_args(2, tmp, u, PZ, 1), STRIP_BWD, s)));
+  } else {  // z backward: tmp -> u
+    SEMFD_TRY(launch_mode_f64_part(tmp, u, p->d_gbf[2][0], p->fld[2], PZ, r[2], r[2], 1, nz, nz, EPI_STORE, none, s));
+    SEMFD_TRY(launch_mode_f64_part(tmp + r[2], u, gba[2], p->fld[2], PZ, o[2], o[2], 1, nz, nz, EPI_UNFOLD, unfold[2],
+                                   s));
+  }
 #undef SEMFD_TRY
   return hipSuccess;
 }

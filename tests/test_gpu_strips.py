@@ -1,0 +1,62 @@
+"""The strip products of mode_strip.hip at the edges of their tiles, planes and axis
+lengths, against the oracle (needs an MI355X).
+
+Bar (FP64): 1e-12 ||u||_inf + 10 x the oracle's own rounding floor (two contraction
+orders), as for every FP64 solve.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+from workloads import normal_noise
+
+pytestmark = pytest.mark.gpu
+
+D, N, C = "dirichlet", "neumann", "periodic"
+BOX = (-1, 1, 0, 1.5, -1, 2)
+
+
+def _check(k, ne, bc, inplace=False):
+    import torch
+    import paper_2310_00226_amd as P
+    prob = O.Problem(k, ne, BOX, 1.25, bc)
+    plan = P.Plan(k, ne, BOX, 1.25, bc)
+    assert plan.shape == prob.shape
+    f = normal_noise(prob.shape, seed=5 + k)
+    want = O.fd_solve(prob, f)
+    floor = np.max(np.abs(want - O.fd_solve(prob, f, order=(0, 1, 2))))
+    fd = torch.from_numpy(f).cuda()
+    u = plan.solve(fd, fd if inplace else None).cpu().numpy()
+    err, bound = np.max(np.abs(u - want)), 1e-12 * np.max(np.abs(want)) + 10 * floor
+    assert err <= bound, (plan.shape, err, bound)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 15, 16, 17, 31, 32, 33, 34, 63, 65, 95, 96])
+@pytest.mark.parametrize("bc", [D, C])
+def test_planes_at_tile_edges(n, bc):
+    """nrep on both sides of a multiple of 16 and 4; y and z in one launch."""
+    ne = n + 1 if bc == D else n
+    other = {D: (4, 8), C: (3, 6)}[bc]
+    _check(1, (other[0], ne, other[1]), bc, inplace=n % 2 == 0)
+    _check(1, (other[1], other[0], ne), bc)
+    _check(1, (ne, other[1], other[0]), bc)
+
+
+@pytest.mark.parametrize("ne,bc", [((97, 98, 99), D), ((96, 95, 98), C), ((97, 33, 161), (D, C, N)),
+                                   ((5, 255, 97), (N, D, C)), ((3, 96, 96), N)])
+def test_separate_axes_at_strip_edges(ne, bc):
+    """Planes just too large for one launch, odd and even strips of columns."""
+    _check(1, ne, bc)
+
+
+@pytest.mark.parametrize("long_axes", [(0,), (1,), (2,), (0, 1), (0, 2), (1, 2)])
+@pytest.mark.parametrize("n,bc", [(511, D), (512, C), (513, N)])
+def test_long_axes(long_axes, n, bc):
+    """The last length a strip takes (nrep = 256) and the first of the tiles, on every
+    set of axes: the two kinds of products hand over to each other."""
+    ne = [6, 3, 4]
+    for a in long_axes:
+        ne[a] = 128
+    prob_axis = {D: 4 * 128 - 1, N: 4 * 128 + 1, C: 4 * 128}[bc]
+    assert prob_axis == n
+    _check(4, tuple(ne), bc)
