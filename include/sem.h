@@ -197,7 +197,9 @@ sem_status sem_solve_lowp(sem_plan *p, sem_prec prec, const double *f, double *u
  * The low-precision mode products of a plan (sem_solve_refined, sem_solve_lowp,
  * the PCG preconditioner, the Cahn-Hilliard stepper, split-BF16 batch entries) run
  * with launch shapes chosen by timing on the first use of each precision: for
- * SEM_F32 the factor-tile rows (128, 96, 64 or 32) of each of the six passes; for
+ * SEM_F32 the factor-tile rows (128, 96, 64 or 32) of each of the six passes (which
+ * single solves take where an axis is longer than 1024 nodes; shorter axes run
+ * products of fixed shape); for
  * SEM_BF16 / SEM_BF16X3 the tile order, g = 1, 2 or 4 column strips of 256 that
  * consecutive workgroups share, and the launch: one workgroup per tile (value g)
  * or one workgroup per compute unit looping over the tiles (value 16 + g).  The

@@ -89,7 +89,7 @@ struct Frag {
 template <class T, int TT, int TC, bool DATA_A, class FS, class FA>
 __device__ __forceinline__ void dual_product(Acc<T, TT, TC>& c, const T* __restrict__ gs, const T* __restrict__ ga,
                                              int ldg, int nk, int t0, FS ds, FA da) {
-  constexpr int U = TT * TC > 1 ? 2 : 4;  // steps per set
+  constexpr int U = TT * TC * (int)sizeof(T) > 8 * (sizeof(T) == 4 ? 2 : 1) ? 2 : 4;  // steps per set
   const int lane = threadIdx.x & 63;
   const unsigned v = (unsigned)((lane >> 4) * ldg + (lane & 15));
   gs += 16 * t0;
@@ -147,12 +147,15 @@ __device__ __forceinline__ float multiply(float v, double lam, const EpiArgs& e)
   return __fdividef(v, (float)spectral_den(lam, e.alpha, e.b1, e.b2));
 }
 
-// Element (row m, column c) of a column strip of W columns: rows of 32 FP64 values
-// span all banks, so odd rows swap their 16-column halves and the two rows that a
-// half-wave reads together do not meet.
+// Element (row m, column c) of a column strip of W columns.  A fragment read takes 16
+// columns of four consecutive rows, FP64 two rows at a time: where a row (pair) spans
+// all 64 banks, every second one swaps its 16-column halves, so that they do not meet.
 template <class T, int W>
 __device__ __forceinline__ int at(int m, int c) {
-  if constexpr (sizeof(T) == 8 && W % 32 == 0) return m * W + (c ^ ((m & 1) << 4));
+  constexpr int SPAN = W * (int)sizeof(T) / 128;  // 1: two rows span the banks
+  if constexpr (sizeof(T) == 8 && SPAN >= 2) return m * W + (c ^ ((m & 1) << 4));
+  else if constexpr (sizeof(T) == 4 && SPAN == 1) return m * W + (c ^ (((m >> 1) & 1) << 4));
+  else if constexpr (sizeof(T) == 4 && SPAN >= 2) return m * W + (c ^ ((m & 3) << 4));
   else return m * W + c;
 }
 
@@ -602,10 +605,19 @@ __global__ void plane_kernel(StripArgs g) {
 
 constexpr size_t LDS_MAX = 160 * 1024;
 constexpr int MAX_WAVES = 16;
+// Largest plane that one block takes: two launches fewer, but a block a plane.  Solve in
+// planes / in separate launches: FP64 31^3 17.2 / 19.5 us, 47^3 21.7 / 21.2, 63^3 25.7 /
+// 23.2, 95^3 59 / 44; FP32 31^3 16.3 / 19.2, 63^3 21.3 / 21.6, 95^3 45 / 34.
+constexpr size_t PLANE_BYTES = 48 * 48 * 8;
 
-// Smallest pitch >= len with pitch mod 32 = want: FP64 reads of 16 rows x 2
-// consecutive values (want 2) or 2 rows x 16 values (want 16) meet no bank twice.
-inline int pitch_mod32(int len, int want) { return (len - want + 31) / 32 * 32 + want; }
+// Smallest pitches >= len at which a fragment read meets no bank twice: 16 rows x 4
+// consecutive values (FP64: 2 at a time), or 4 (2) rows x 16 values.
+inline int pitch_rows(int len, int elem) {
+  return elem == 8 ? (len - 2 + 31) / 32 * 32 + 2 : (len - 4 + 63) / 64 * 64 + 4;
+}
+inline int pitch_cols(int len, int elem) {
+  return elem == 8 ? (len - 16 + 31) / 32 * 32 + 16 : (len - 16 + 63) / 64 * 64 + 16;
+}
 inline int pad16(int n) { return (n + 15) / 16 * 16; }
 // elements of a line in a strip
 inline int strip_len(const StripAxis& a) { return 2 * pad4(a.nrep); }
@@ -630,58 +642,73 @@ inline int strip_cols(long P, long Q, size_t line_bytes) {
 
 }  // namespace stripk
 
-// Waves of a strip block take one tile of 16 modes each, 16 waves at most.
+// Waves of a strip block take one tile of 16 modes each (FP32: one or two), 16 waves
+// at most.
 bool strip_axis_ok(const StripAxis& a, int elem) {
-  return a.nrep <= 16 * stripk::MAX_WAVES && (size_t)stripk::pitch_mod32(stripk::strip_len(a), 2) * elem * 16 <= stripk::LDS_MAX;
+  return a.nrep <= 16 * stripk::MAX_WAVES * (elem == 4 ? 2 : 1) && (size_t)stripk::pitch_rows(stripk::strip_len(a), elem) * elem * 16 <= stripk::LDS_MAX;
 }
 
 bool strip_plane_ok(const StripAxis& ay, const StripAxis& az, int elem) {
   using namespace stripk;
-  return strip_axis_ok(ay, elem) && strip_axis_ok(az, elem) &&
-         (size_t)pad16(ay.n) * (pitch_mod32(strip_len(az), 2) + pitch_mod32(pad16(az.n), 16)) * elem <= LDS_MAX;
+  return (size_t)ay.n * az.n * elem <= PLANE_BYTES && strip_axis_ok(ay, elem) && strip_axis_ok(az, elem) &&
+         (size_t)pad16(ay.n) * (pitch_rows(strip_len(az), elem) + pitch_cols(pad16(az.n), elem)) * elem <= LDS_MAX;
 }
 
-template <class T, int OP, bool SPECTRAL = false>
+template <class T, int TT, int OP, bool SPECTRAL>
 static hipError_t col_launch(StripArgs g, hipStream_t s) {
   using namespace stripk;
-  const int waves = (g.ax.nrep + 15) / 16;
+  const int waves = (g.ax.nrep + 16 * TT - 1) / (16 * TT);
   const size_t line = (size_t)strip_len(g.ax) * sizeof(T);
   const int tc = strip_cols(g.P, g.Q, line);
   g.ntiles = (g.Q + 16 * tc - 1) / (16 * tc) * g.P;
   const long blocks = (g.ntiles + 7) / 8 * 8;
-  if (tc == 1) return launch(col_kernel<T, 1, 1, OP, SPECTRAL>, g, blocks, waves, 16 * line, s);
-  return launch(col_kernel<T, 1, 2, OP, SPECTRAL>, g, blocks, waves, 32 * line, s);
+  if (tc == 1) return launch(col_kernel<T, TT, 1, OP, SPECTRAL>, g, blocks, waves, 16 * line, s);
+  return launch(col_kernel<T, TT, 2, OP, SPECTRAL>, g, blocks, waves, 32 * line, s);
+}
+
+template <class T, int OP, bool SPECTRAL = false>
+static hipError_t col_tiles(const StripArgs& g, hipStream_t s) {
+  if constexpr (sizeof(T) == 4)
+    if (g.ax.nrep > 16 * stripk::MAX_WAVES) return col_launch<T, 2, OP, SPECTRAL>(g, s);
+  return col_launch<T, 1, OP, SPECTRAL>(g, s);
 }
 
 template <class T>
 hipError_t launch_strip_col(const StripArgs& g, int op, hipStream_t s) {
   if (!strip_axis_ok(g.ax, sizeof(T)) || g.P < 1 || g.Q < 1 || g.Q > STRIP_MAX_Q) return hipErrorInvalidValue;
-  if (op == STRIP_FWD) return col_launch<T, STRIP_FWD>(g, s);
-  if (op == STRIP_BWD) return col_launch<T, STRIP_BWD>(g, s);
+  if (op == STRIP_FWD) return col_tiles<T, STRIP_FWD>(g, s);
+  if (op == STRIP_BWD) return col_tiles<T, STRIP_BWD>(g, s);
   if (g.P != 1) return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 8)
-    if (g.epi.kind) return col_launch<T, STRIP_MUL, true>(g, s);
-  return col_launch<T, STRIP_MUL>(g, s);
+    if (g.epi.kind) return col_tiles<T, STRIP_MUL, true>(g, s);
+  return col_tiles<T, STRIP_MUL>(g, s);
+}
+
+template <class T, class TI, int TT, int OP>
+static hipError_t row_launch(StripArgs g, hipStream_t s) {
+  using namespace stripk;
+  const int waves = (g.ax.nrep + 16 * TT - 1) / (16 * TT);
+  g.stride = pitch_rows(strip_len(g.ax), sizeof(T));
+  const size_t line = (size_t)g.stride * sizeof(T);
+  const int tc = strip_cols(1, g.P, line);
+  g.ntiles = (g.P + 16 * tc - 1) / (16 * tc);
+  const long blocks = (g.ntiles + 7) / 8 * 8;
+  if (tc == 1) return launch(row_kernel<T, TI, TT, 1, OP>, g, blocks, waves, 16 * line, s);
+  return launch(row_kernel<T, TI, TT, 2, OP>, g, blocks, waves, 32 * line, s);
 }
 
 template <class T, class TI, int OP>
-static hipError_t row_launch(StripArgs g, hipStream_t s) {
-  using namespace stripk;
-  const int waves = (g.ax.nrep + 15) / 16;
-  g.stride = pitch_mod32(strip_len(g.ax), 2);
-  const int tc = strip_cols(1, g.P, (size_t)g.stride * sizeof(T));
-  g.ntiles = (g.P + 16 * tc - 1) / (16 * tc);
-  const size_t lds = (size_t)g.stride * 16 * tc * sizeof(T);
-  const long blocks = (g.ntiles + 7) / 8 * 8;
-  if (tc == 1) return launch(row_kernel<T, TI, 1, 1, OP>, g, blocks, waves, lds, s);
-  return launch(row_kernel<T, TI, 1, 2, OP>, g, blocks, waves, lds, s);
+static hipError_t row_tiles(const StripArgs& g, hipStream_t s) {
+  if constexpr (sizeof(T) == 4)
+    if (g.ax.nrep > 16 * stripk::MAX_WAVES) return row_launch<T, TI, 2, OP>(g, s);
+  return row_launch<T, TI, 1, OP>(g, s);
 }
 
 template <class T, class TI>
 hipError_t launch_strip_row(const StripArgs& g, int op, hipStream_t s) {
   if (!strip_axis_ok(g.ax, sizeof(T)) || g.P < 1 || g.ldx < g.ax.n) return hipErrorInvalidValue;
-  if (op == STRIP_FWD) return row_launch<T, TI, STRIP_FWD>(g, s);
-  return row_launch<T, T, STRIP_BWD>(g, s);
+  if (op == STRIP_FWD) return row_tiles<T, TI, STRIP_FWD>(g, s);
+  return row_tiles<T, T, STRIP_BWD>(g, s);
 }
 
 template <class T, class TI>
@@ -689,8 +716,8 @@ hipError_t launch_strip_plane(StripArgs g, int op, hipStream_t s) {
   using namespace stripk;
   if (!strip_plane_ok(g.ay, g.ax, sizeof(T)) || g.P < 1 || g.ldx < g.ax.n || (op == STRIP_BWD && g.ldx != g.ax.n))
     return hipErrorInvalidValue;
-  g.stride = pitch_mod32(strip_len(g.ax), 2);
-  g.stride2 = pitch_mod32(pad16(g.ax.n), 16);
+  g.stride = pitch_rows(strip_len(g.ax), sizeof(T));
+  g.stride2 = pitch_cols(pad16(g.ax.n), sizeof(T));
   const size_t lds = (size_t)pad16(g.ay.n) * (g.stride + g.stride2) * sizeof(T);
   // waves: the larger of the two products' tiles in as few equal rounds as possible
   const int items = std::max((g.ay.n + 15) / 16 * ((g.ax.nrep + 15) / 16), (g.ax.n + 15) / 16 * ((g.ay.nrep + 15) / 16));
@@ -703,5 +730,10 @@ hipError_t launch_strip_plane(StripArgs g, int op, hipStream_t s) {
 template hipError_t launch_strip_col<double>(const StripArgs&, int, hipStream_t);
 template hipError_t launch_strip_row<double, double>(const StripArgs&, int, hipStream_t);
 template hipError_t launch_strip_plane<double, double>(StripArgs, int, hipStream_t);
+template hipError_t launch_strip_col<float>(const StripArgs&, int, hipStream_t);
+template hipError_t launch_strip_row<float, double>(const StripArgs&, int, hipStream_t);
+template hipError_t launch_strip_row<float, float>(const StripArgs&, int, hipStream_t);
+template hipError_t launch_strip_plane<float, double>(StripArgs, int, hipStream_t);
+template hipError_t launch_strip_plane<float, float>(StripArgs, int, hipStream_t);
 
 }  // namespace semfd

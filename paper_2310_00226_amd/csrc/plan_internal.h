@@ -49,6 +49,9 @@ struct sem_plan {
   int lpf_frow2[3] = {0, 0, 0};
   long lpf_plane[3] = {0, 0, 0};
   double* d_lamf[3] = {nullptr, nullptr, nullptr};  // eigenvalues in folded mode order
+  // FP32 strip factors [axis][forward symmetric, antisymmetric, backward symmetric,
+  // antisymmetric], the layout of d_gff / d_gbf (pitch fld); one allocation per axis
+  float* lps[3][4] = {};
   int lp_ready = 0;
   // tuned launch shapes per precision (index sem_prec) and pass: FP32 tile rows,
   // BF16 tile order group (lp_tune)

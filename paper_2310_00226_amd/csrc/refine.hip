@@ -12,9 +12,11 @@
 //
 // Each low-precision solve is six rotating mode products:
 //   (x,y,z) -z-> (z,x,y) -y-> (y,z,x) -x,divide-> (x,y,z) -z-> (z,x,y) -y-> (y,z,x) -x-> u
+// FP32 solves with axes of up to 1024 nodes run the reflection-split products of
+// mode_strip.hip instead, in the caller's axis order.
 // Intermediates live in the workspace with their contiguous axis padded to a
-// multiple of 8 elements (16-byte rows for BF16).  FP32 runs the register-staged
-// kernels of mode_lp.hip; BF16 and split BF16 run the direct-to-LDS kernels of
+// multiple of 8 elements (16-byte rows for BF16).  FP32 with longer axes runs the
+// register-staged kernels of mode_lp.hip; BF16 and split BF16 run the direct-to-LDS kernels of
 // mode_dma.hip, with every operand in BF16 planes (split: a hi plane and a lo
 // plane): the right-hand side is converted once, the residual is written in that
 // format directly.
@@ -126,6 +128,10 @@ void release_lowp(sem_plan* p) {
       (void)hipFree(p->lpf[a][d]);
       p->lp_f32[a][d] = p->lp_hi[a][d] = p->lp_lo[a][d] = p->lpf[a][d] = nullptr;
     }
+  for (auto& axis : p->lps) {
+    (void)hipFree(axis[0]);
+    for (float*& g : axis) g = nullptr;
+  }
   for (int a = 0; a < 3; ++a) {
     (void)hipFree(p->d_lamf[a]);
     p->d_lamf[a] = nullptr;
@@ -199,6 +205,27 @@ static sem_status ensure_lowp(sem_plan* p) {
         release_lowp(p);
         return hip_fail(e, "folded factor upload");
       }
+    }
+    // strip factors: G[m][l] = A[l][m], as the FP64 ones, four blocks in one allocation
+    {
+      const int fld = p->fld[a];
+      const size_t block = (size_t)(fld + 128) * fld;
+      std::vector<float> g(4 * block, 0.0f);
+      for (int i = 0; i < 4; ++i) {
+        const int rows = i == 1 ? no : nr, cols = i == 3 ? no : nr;
+        for (int l = 0; l < rows; ++l)
+          for (int m = 0; m < cols; ++m)
+            g[i * block + (size_t)m * fld + l] = (float)(i < 2 ? ax.ffold[(size_t)(l + i * nr) * nr + m]
+                                                        : i == 2 ? ax.bfold_sym[(size_t)l * nr + m]
+                                                                 : ax.bfold_anti[(size_t)l * no + m]);
+      }
+      hipError_t e;
+      if ((e = hipMalloc(&p->lps[a][0], g.size() * 4)) != hipSuccess ||
+          (e = hipMemcpy(p->lps[a][0], g.data(), g.size() * 4, hipMemcpyHostToDevice)) != hipSuccess) {
+        release_lowp(p);
+        return hip_fail(e, "strip factor upload");
+      }
+      for (int i = 1; i < 4; ++i) p->lps[a][i] = p->lps[a][0] + i * block;
     }
     hipError_t e;
     if ((e = hipMalloc(&p->d_lamf[a], sizeof(double) * n)) != hipSuccess ||
@@ -373,6 +400,74 @@ static hipError_t lp_fd_folded(sem_plan* p, const LpWork& w, const Spectral& sp,
   return launch_unfold_accum((const float*)w.t1, dpitch(p), u, p->dims, fa, first, norms, p->stream, w.unfold_dot);
 }
 
+static StripAxis strip_axis(const sem_plan* p, int a) {
+  return StripAxis{p->dims[a], p->ax[a].nrep, p->ax[a].nodd, p->bc[a] == SEM_BC_PERIODIC ? 1 : 0};
+}
+
+// Whether the FP32 products of a plan run on strips (every axis up to 1024 nodes).
+static bool f32_strips(const sem_plan* p) {
+  for (int a = 0; a < 3; ++a)
+    if (!strip_axis_ok(strip_axis(p, a), sizeof(float))) return false;
+  return (long)p->dims[1] * p->dims[2] <= STRIP_MAX_Q;
+}
+
+// The FP32 FD application on strips: src -> t0 (z), in place (y, x, y), t0 -> u.  Half
+// the flops of the rotating passes, whose transforms are dense.
+static hipError_t f32_strip_fd(sem_plan* p, const LpWork& w, const Spectral& sp, const double* f64_src, double* u,
+                               int first, unsigned long long* norms) {
+  const int nx = p->dims[0], ny = p->dims[1], nz = p->dims[2];
+  auto args = [&](int a, const void* x, void* y, long P, long Q) {
+    StripArgs g;
+    g.x = x;
+    g.y = y;
+    g.fs = p->lps[a][0];
+    g.fa = p->lps[a][1];
+    g.bs = p->lps[a][2];
+    g.ba = p->lps[a][3];
+    g.ldg = p->fld[a];
+    g.ax = strip_axis(p, a);
+    g.P = P;
+    g.Q = Q;
+    g.ldx = nz;
+    g.epi.lx = p->d_lamf[0];
+    g.epi.ly = p->d_lamf[1];
+    g.epi.lz = p->d_lamf[2];
+    g.epi.alpha = sp.alpha;
+    g.epi.b1 = sp.b1;
+    g.epi.b2 = sp.b2;
+    g.epi.nz = nz;
+    return g;
+  };
+  const bool plane = strip_plane_ok(strip_axis(p, 1), strip_axis(p, 2), sizeof(float));
+  const void* src = f64_src ? (const void*)f64_src : w.r;
+  StripArgs in = args(2, src, w.t0, plane ? nx : (long)nx * ny, 1), out = args(2, w.t0, u, in.P, 1);
+  in.ldx = f64_src ? nz : w.ldr;
+  out.first = first;
+  out.norms = norms;
+  hipStream_t s = p->stream;
+  hipError_t e;
+  if (plane) {
+    for (StripArgs* g : {&in, &out}) {
+      g->ay = strip_axis(p, 1);
+      g->fs2 = p->lps[1][0];
+      g->fa2 = p->lps[1][1];
+      g->bs2 = p->lps[1][2];
+      g->ba2 = p->lps[1][3];
+      g->ldg2 = p->fld[1];
+    }
+    e = f64_src ? launch_strip_plane<float, double>(in, STRIP_FWD, s)
+                : launch_strip_plane<float, float>(in, STRIP_FWD, s);
+  } else {
+    e = f64_src ? launch_strip_row<float, double>(in, STRIP_FWD, s) : launch_strip_row<float, float>(in, STRIP_FWD, s);
+    if (e == hipSuccess) e = launch_strip_col<float>(args(1, w.t0, w.t0, nx, nz), STRIP_FWD, s);
+  }
+  if (e != hipSuccess) return e;
+  if ((e = launch_strip_col<float>(args(0, w.t0, w.t0, 1, (long)ny * nz), STRIP_MUL, s)) != hipSuccess) return e;
+  if (plane) return launch_strip_plane<float, float>(out, STRIP_BWD, s);
+  if ((e = launch_strip_col<float>(args(1, w.t0, w.t0, nx, nz), STRIP_BWD, s)) != hipSuccess) return e;
+  return launch_strip_row<float, float>(out, STRIP_BWD, s);
+}
+
 // Pass s (0..5) of the FP32 sequence  src -> t0 -> t1 -> t0 -> t1 -> t0 -> u.
 // With u == nullptr the last pass stores FP32 into t1 instead of accumulating
 // into u (the stand-in the tuner times).
@@ -449,6 +544,7 @@ static LpPass f32_pass(sem_plan* p, const LpWork& w, const Spectral& sp, int s, 
 hipError_t lp_fd(sem_plan* p, const LpWork& w, const Spectral& sp, const double* f64_src, double* u, int first,
                  unsigned long long* norms) {
   if (w.prec != SEM_F32) return lp_fd_folded(p, w, sp, f64_src, u, first, norms);
+  if (f32_strips(p)) return f32_strip_fd(p, w, sp, f64_src, u, first, norms);
   for (int s = 0; s < 6; ++s) {
     const hipError_t e = launch_mode_lp(f32_pass(p, w, sp, s, f64_src, u, first, norms), p->stream);
     if (e != hipSuccess) return e;
@@ -547,10 +643,6 @@ sem_status lp_tune(sem_plan* p, const LpWork& w) {
   }
   p->tuned[prec] = 1;
   return SEM_OK;
-}
-
-static StripAxis strip_axis(const sem_plan* p, int a) {
-  return StripAxis{p->dims[a], p->ax[a].nrep, p->ax[a].nodd, p->bc[a] == SEM_BC_PERIODIC ? 1 : 0};
 }
 
 // FP64 FD application on the reflection-split transforms (the plan's folded

@@ -42,10 +42,10 @@ def test_planes_at_tile_edges(n, bc):
     _check(1, (ne, other[1], other[0]), bc)
 
 
-@pytest.mark.parametrize("ne,bc", [((97, 98, 99), D), ((96, 95, 98), C), ((97, 33, 161), (D, C, N)),
+@pytest.mark.parametrize("ne,bc", [((5, 49, 49), D), ((5, 50, 49), D), ((97, 98, 99), D), ((96, 95, 98), C), ((97, 33, 161), (D, C, N)),
                                    ((5, 255, 97), (N, D, C)), ((3, 96, 96), N)])
 def test_separate_axes_at_strip_edges(ne, bc):
-    """Planes just too large for one launch, odd and even strips of columns."""
+    """The largest plane of one launch and the first past it, odd and even strips."""
     _check(1, ne, bc)
 
 
@@ -60,3 +60,40 @@ def test_long_axes(long_axes, n, bc):
     prob_axis = {D: 4 * 128 - 1, N: 4 * 128 + 1, C: 4 * 128}[bc]
     assert prob_axis == n
     _check(4, tuple(ne), bc)
+
+
+def _check_f32(k, ne, bc):
+    """FP32 products inside the refinement: the bar of every refined solve, 1e-10 of the
+    oracle (a wrong product would not contract)."""
+    import torch
+    import paper_2310_00226_amd as P
+    prob = O.Problem(k, ne, BOX, 1.25, bc)
+    plan = P.Plan(k, ne, BOX, 1.25, bc)
+    f = normal_noise(prob.shape, seed=5 + k)
+    want = O.fd_solve(prob, f)
+    u, it, rel, st = plan.solve_refined(torch.from_numpy(f).cuda(), prec="f32", tol=1e-12)
+    assert st == 0 and it <= 6
+    assert np.max(np.abs(u.cpu().numpy() - want)) <= 1e-10 * np.max(np.abs(want))
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 17, 32, 33, 65, 129])
+@pytest.mark.parametrize("bc", [D, C])
+def test_f32_planes_and_tiles(n, bc):
+    ne = n + 1 if bc == D else n
+    a, b = {D: (4, 8), C: (3, 6)}[bc]
+    for mesh in ((a, ne, b), (b, a, ne), (ne, b, a)):
+        _check_f32(1, mesh, bc)
+
+
+@pytest.mark.parametrize("ne,bc", [((4, 68, 68), D), ((4, 68, 69), D), ((97, 138, 141), D), ((33, 161, 150), (D, C, N)), ((140, 40, 200), N)])
+def test_f32_separate_axes(ne, bc):
+    _check_f32(1, ne, bc)
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("ne,bc", [(128, N), (255, D), (256, C), (256, N)])
+def test_f32_long_axes(axis, ne, bc):
+    """Two tiles a wave (nrep = 257 .. 512), and the first length past the strips."""
+    mesh = [6, 3, 4]
+    mesh[axis] = ne
+    _check_f32(4, tuple(mesh), bc)
