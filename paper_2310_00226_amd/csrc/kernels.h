@@ -77,17 +77,15 @@ struct StripAxis {
   int n = 0, nrep = 0, nodd = 0, per = 0;
 };
 enum { STRIP_FWD = 0, STRIP_BWD = 1, STRIP_MUL = 2 };
-// Factors G[m][l] of pitch ldg (>= nrep rounded up to 16) with 17 zero rows behind
-// the contraction: fs, fa forward symmetric / antisymmetric (modes x representatives),
-// bs, ba backward (representatives x modes of the block).  Modes are in folded order.
+// Factors in fragment order (strip_pack) with elements of the data's type: fs, fa
+// forward symmetric / antisymmetric (modes x representatives), bs, ba backward
+// (representatives x modes of the block).  Modes are in folded order.
 struct StripArgs {
   const void* x = nullptr;
   void* y = nullptr;  // may be x where their types and pitches agree
   const void *fs = nullptr, *fa = nullptr, *bs = nullptr, *ba = nullptr;
-  int ldg = 0;
   // planes: the y axis (ay) and its factors; ax and the factors above are the z axis
   const void *fs2 = nullptr, *fa2 = nullptr, *bs2 = nullptr, *ba2 = nullptr;
-  int ldg2 = 0;
   StripAxis ax, ay;
   // columns: X[p][m][q], p < P, q < Q; rows: P rows of pitch ldx; planes: P planes
   // of ay.n rows of pitch ldx
@@ -98,9 +96,40 @@ struct StripArgs {
   int first = 1;
   unsigned long long* norms = nullptr;
   // set by the launchers
+  int tiles = 0, tiles2 = 0;  // 16-mode tiles in a factor's steps
   int stride = 0, stride2 = 0;
   long ntiles = 0;
 };
+// The order in which the strips read a factor: blocks of VU = 16 / sizeof(T) contraction
+// steps of 4 rows, in each the tiles of 16 modes, in each 64 lanes of VU values, lane
+// (k % 4, l % 16) holding rows 4 step + k % 4 of column l.  A wave's load of a block is
+// 1 KB in one piece (in row order it was VU loads of four pieces).
+inline int strip_tiles(int nrep) { return (nrep + 31) / 32 * 2; }
+template <class T>
+size_t strip_pack_elems(int nrep) {
+  const int vu = 16 / (int)sizeof(T);
+  return (size_t)(((nrep + 3) / 4 + 8 + vu - 1) / vu) * strip_tiles(nrep) * 64 * vu;  // 8 zero steps read ahead
+}
+// Factor A (L x M, row-major of pitch lda; rows l are outputs) into out, zero-filled.
+template <class T>
+void strip_pack(const double* a, int lda, int L, int M, int nrep, T* out) {
+  const int vu = 16 / (int)sizeof(T), tiles = strip_tiles(nrep);
+  for (int l = 0; l < L; ++l)
+    for (int m = 0; m < M; ++m) {
+      const int step = m / 4, lane = (m % 4) * 16 + l % 16;
+      out[(((size_t)(step / vu) * tiles + l / 16) * 64 + lane) * vu + step % vu] = (T)a[(size_t)l * lda + m];
+    }
+}
+// All four factors of an axis (ffold n x nrep, bfold_sym nrep x nrep, bfold_anti nrep x
+// nodd) one after the other: 4 strip_pack_elems elements, zero-filled by the caller.
+template <class T>
+void strip_pack_axis(const double* ffold, const double* bsym, const double* banti, int nrep, int nodd, T* out) {
+  const size_t block = strip_pack_elems<T>(nrep);
+  strip_pack(ffold, nrep, nrep, nrep, nrep, out);
+  strip_pack(ffold + (size_t)nrep * nrep, nrep, nodd, nrep, nrep, out + block);
+  strip_pack(bsym, nrep, nrep, nrep, nrep, out + 2 * block);
+  strip_pack(banti, nodd, nrep, nodd, nrep, out + 3 * block);
+}
 constexpr long STRIP_MAX_Q = 1L << 22;  // 32-bit offsets of 64 rows inside a strip's base
 // Whether the strips take an axis / a pair of axes with elements of `elem` bytes.
 bool strip_axis_ok(const StripAxis& a, int elem);

@@ -14,8 +14,8 @@
 //  * along x the forward product, the spectral multiplier and the backward product
 //    are one launch (the coefficients stay in LDS);
 //  * small (y, z) planes do z and y in one launch: three launches for a solve.
-// The factors are not staged: a wave reads its 4 x 16 fragments from L1 / L2 four
-// contraction steps ahead (an FP64 fragment pair feeds 2 TC MFMAs of 64 cycles).
+// The factors are not staged: a wave reads its fragments from L1 / L2 four contraction
+// steps ahead, in 1 KB pieces (an FP64 fragment pair feeds 2 TC MFMAs of 64 cycles).
 // What bounds them is the MFMA rate and the padding of the modes to 16; the strips'
 // loads and stores are overlapped by the other blocks of the CU.
 #include <hip/hip_runtime.h>
@@ -63,44 +63,49 @@ struct Acc {
   typename Mfma<T>::acc_t s[TT][TC], a[TT][TC];
 };
 
-// Factor fragments of U contraction steps, symmetric and antisymmetric.
-template <class T, int TT, int U>
+// Factor fragments of U contraction steps, symmetric and antisymmetric, from factors
+// in fragment order (strip_pack): one 16-byte load per lane holds VU steps.
+constexpr int U = 4;
+template <class T, int TT>
 struct Frag {
-  T s[U][TT], a[U][TT];
-  // rows 4 k0 .. of the factors, v = the lane's offset
-  __device__ __forceinline__ void load(const T* __restrict__ gs, const T* __restrict__ ga, int ldg, int k0,
-                                       unsigned v) {
+  static constexpr int VU = 16 / (int)sizeof(T), NV = U / VU;
+  typedef T vec_t __attribute__((ext_vector_type(VU)));
+  vec_t s[NV][TT], a[NV][TT];
+  // steps k0 .. k0 + U - 1 (k0 a multiple of U)
+  __device__ __forceinline__ void load(const vec_t* __restrict__ gs, const vec_t* __restrict__ ga, int tiles, int k0) {
+    const unsigned lane = threadIdx.x & 63;
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int h = 0; h < NV; ++h)
 #pragma unroll
       for (int i = 0; i < TT; ++i) {
-        s[u][i] = (gs + (size_t)(4 * (k0 + u)) * ldg + 16 * i)[v];
-        a[u][i] = (ga + (size_t)(4 * (k0 + u)) * ldg + 16 * i)[v];
+        const size_t at = ((size_t)(k0 / VU + h) * tiles + i) * 64;  // uniform
+        s[h][i] = (gs + at)[lane];
+        a[h][i] = (ga + at)[lane];
       }
   }
 };
 
 // Both halves of one product for the mode tiles t0 .. t0 + TT - 1: s += G_s^T ds,
-// a += G_a^T da over nk steps of 4 contraction rows, factors G[m][l] of pitch ldg
-// (rows behind the contraction are zero; up to 4 U of them are read).  ds(k, j),
-// da(k, j): this lane's data element of column tile j in step k.  DATA_A: the data
-// is the first operand, so that the data index runs along the accumulator's rows.
-// Two sets of fragments take turns, without copies: a copy would wait for its load.
+// a += G_a^T da over nk steps of 4 contraction rows.  ds(k, j), da(k, j): this lane's
+// data element of column tile j in step k.  DATA_A: the data is the first operand, so
+// that the data index runs along the accumulator's rows.
+// Two sets of U steps take turns, without copies: a copy would wait for its load.
+// Vector memory answers a CU in order, so a fragment also waits for the strips that
+// other blocks of the CU are loading: with U = 2 FP64 511^3 took 8298 instead of 7670 us
+// (U = 6 the same, U = 8 8056).
 template <class T, int TT, int TC, bool DATA_A, class FS, class FA>
-__device__ __forceinline__ void dual_product(Acc<T, TT, TC>& c, const T* __restrict__ gs, const T* __restrict__ ga,
-                                             int ldg, int nk, int t0, FS ds, FA da) {
-  constexpr int U = TT * TC * (int)sizeof(T) > 8 * (sizeof(T) == 4 ? 2 : 1) ? 2 : 4;  // steps per set
-  const int lane = threadIdx.x & 63;
-  const unsigned v = (unsigned)((lane >> 4) * ldg + (lane & 15));
-  gs += 16 * t0;
-  ga += 16 * t0;
+__device__ __forceinline__ void dual_product(Acc<T, TT, TC>& c, const void* fs, const void* fa, int tiles, int nk,
+                                             int t0, FS ds, FA da) {
+  typedef Frag<T, TT> F;
+  const typename F::vec_t* __restrict__ gs = (const typename F::vec_t*)fs + (size_t)t0 * 64;
+  const typename F::vec_t* __restrict__ ga = (const typename F::vec_t*)fa + (size_t)t0 * 64;
 #pragma unroll
   for (int i = 0; i < TT; ++i)
 #pragma unroll
     for (int j = 0; j < TC; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) c.s[i][j][r] = c.a[i][j][r] = T(0);
-  auto mul = [&](const Frag<T, TT, U>& f, int u, int k) {
+  auto mul = [&](const F& f, int u, int k) {
     T s[TC], a[TC];
 #pragma unroll
     for (int j = 0; j < TC; ++j) {
@@ -108,25 +113,27 @@ __device__ __forceinline__ void dual_product(Acc<T, TT, TC>& c, const T* __restr
       a[j] = da(k, j);
     }
 #pragma unroll
-    for (int i = 0; i < TT; ++i)
+    for (int i = 0; i < TT; ++i) {
+      const T gs1 = f.s[u / F::VU][i][u % F::VU], ga1 = f.a[u / F::VU][i][u % F::VU];
 #pragma unroll
       for (int j = 0; j < TC; ++j) {
-        c.s[i][j] = DATA_A ? Mfma<T>::mac(s[j], f.s[u][i], c.s[i][j]) : Mfma<T>::mac(f.s[u][i], s[j], c.s[i][j]);
-        c.a[i][j] = DATA_A ? Mfma<T>::mac(a[j], f.a[u][i], c.a[i][j]) : Mfma<T>::mac(f.a[u][i], a[j], c.a[i][j]);
+        c.s[i][j] = DATA_A ? Mfma<T>::mac(s[j], gs1, c.s[i][j]) : Mfma<T>::mac(gs1, s[j], c.s[i][j]);
+        c.a[i][j] = DATA_A ? Mfma<T>::mac(a[j], ga1, c.a[i][j]) : Mfma<T>::mac(ga1, a[j], c.a[i][j]);
       }
+    }
   };
-  Frag<T, TT, U> f0, f1;
-  f0.load(gs, ga, ldg, 0, v);
+  F f0, f1;
+  f0.load(gs, ga, tiles, 0);
   int k = 0;
   for (; k + 2 * U <= nk; k += 2 * U) {
-    f1.load(gs, ga, ldg, k + U, v);
+    f1.load(gs, ga, tiles, k + U);
 #pragma unroll
     for (int u = 0; u < U; ++u) mul(f0, u, k + u);
-    f0.load(gs, ga, ldg, k + 2 * U, v);
+    f0.load(gs, ga, tiles, k + 2 * U);
 #pragma unroll
     for (int u = 0; u < U; ++u) mul(f1, u, k + U + u);
   }
-  if (k + U < nk) f1.load(gs, ga, ldg, k + U, v);
+  if (k + U < nk) f1.load(gs, ga, tiles, k + U);
 #pragma unroll
   for (int u = 0; u < U; ++u)
     if (k + u < nk) mul(f0, u, k + u);
@@ -154,7 +161,7 @@ template <class T, int W>
 __device__ __forceinline__ int at(int m, int c) {
   constexpr int SPAN = W * (int)sizeof(T) / 128;  // 1: two rows span the banks
   if constexpr (sizeof(T) == 8 && SPAN >= 2) return m * W + (c ^ ((m & 1) << 4));
-  else if constexpr (sizeof(T) == 4 && SPAN == 1) return m * W + (c ^ (((m >> 1) & 1) << 4));
+  else if constexpr (sizeof(T) == 4 && SPAN == 1) return m * W + (c ^ (((m ^ (m >> 1)) & 1) << 4));
   else if constexpr (sizeof(T) == 4 && SPAN >= 2) return m * W + (c ^ ((m & 3) << 4));
   else return m * W + c;
 }
@@ -239,7 +246,7 @@ __global__ void col_kernel(StripArgs g) {
 
   Acc<T, TT, TC> c;
   if constexpr (OP != STRIP_BWD) {
-    dual_product<T, TT, TC, false>(c, (const T*)g.fs, (const T*)g.fa, g.ldg, nk, t0, ds, da);
+    dual_product<T, TT, TC, false>(c, g.fs, g.fa, g.tiles, nk, t0, ds, da);
   }
   // output addresses: a uniform row of the accumulator register plus the lane's
   // offset; mirrored rows run the other way
@@ -289,7 +296,7 @@ __global__ void col_kernel(StripArgs g) {
     }
     __syncthreads();
   }
-  dual_product<T, TT, TC, false>(c, (const T*)g.bs, (const T*)g.ba, g.ldg, nk, t0, ds, da);
+  dual_product<T, TT, TC, false>(c, g.bs, g.ba, g.tiles, nk, t0, ds, da);
 #pragma unroll
   for (int i = 0; i < TT; ++i)
 #pragma unroll
@@ -414,7 +421,7 @@ __global__ void row_kernel(StripArgs g) {
   const unsigned w0 = (unsigned)(Mfma<T>::RL * fk * ax.n);  // the lane's part of an output row's address
   if constexpr (OP == STRIP_FWD) {
     T* y = reinterpret_cast<T*>(g.y) + (size_t)p0 * ax.n;
-    dual_product<T, TT, TC, true>(c, (const T*)g.fs, (const T*)g.fa, g.ldg, nk, t0, ds, da);
+    dual_product<T, TT, TC, true>(c, g.fs, g.fa, g.tiles, nk, t0, ds, da);
 #pragma unroll
     for (int j = 0; j < TC; ++j)
 #pragma unroll
@@ -431,7 +438,7 @@ __global__ void row_kernel(StripArgs g) {
       }
   } else {
     double* y = reinterpret_cast<double*>(g.y) + (size_t)p0 * ax.n;
-    dual_product<T, TT, TC, true>(c, (const T*)g.bs, (const T*)g.ba, g.ldg, nk, t0, ds, da);
+    dual_product<T, TT, TC, true>(c, g.bs, g.ba, g.tiles, nk, t0, ds, da);
 #pragma unroll
     for (int j = 0; j < TC; ++j)
 #pragma unroll
@@ -522,7 +529,7 @@ __global__ void plane_kernel(StripArgs g) {
       const int s = w / tiles_z, t = w - s * tiles_z;
       const T* line = Z + (16 * s + fr) * sz;
       dual_product<T, 1, 1, true>(
-          c, (const T*)g.fs, (const T*)g.fa, g.ldg, Kz >> 2, t, [&](int k, int) { return line[4 * k + fk]; },
+          c, g.fs, g.fa, g.tiles, Kz >> 2, t, [&](int k, int) { return line[4 * k + fk]; },
           [&](int k, int) { return line[Kz + 4 * k + fk]; });
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -539,7 +546,7 @@ __global__ void plane_kernel(StripArgs g) {
       const int s = w / tiles_y, t = w - s * tiles_y;
       const T* col = Y + 16 * s + fr;
       dual_product<T, 1, 1, false>(
-          c, (const T*)g.fs2, (const T*)g.fa2, g.ldg2, Ky >> 2, t,
+          c, g.fs2, g.fa2, g.tiles2, Ky >> 2, t,
           [&](int k, int) {
             const int m = min(4 * k + fk, ay.nrep - 1);
             return col[m * sy] + col[refl(m, ay) * sy];
@@ -562,7 +569,7 @@ __global__ void plane_kernel(StripArgs g) {
       const int s = w / tiles_y, t = w - s * tiles_y;
       const T* col = Y + 16 * s + fr;
       dual_product<T, 1, 1, false>(
-          c, (const T*)g.bs2, (const T*)g.ba2, g.ldg2, Ky >> 2, t,
+          c, g.bs2, g.ba2, g.tiles2, Ky >> 2, t,
           [&](int k, int) { return col[min(4 * k + fk, ay.nrep - 1) * sy]; },
           [&](int k, int) { return col[min(ay.nrep + 4 * k + fk, ay.n - 1) * sy]; });
       const int q = 16 * s + fr;
@@ -584,7 +591,7 @@ __global__ void plane_kernel(StripArgs g) {
       const int s = w / tiles_z, t = w - s * tiles_z;
       const T* line = Z + (16 * s + fr) * sz;
       dual_product<T, 1, 1, true>(
-          c, (const T*)g.bs, (const T*)g.ba, g.ldg, Kz >> 2, t,
+          c, g.bs, g.ba, g.tiles, Kz >> 2, t,
           [&](int k, int) { return line[min(4 * k + fk, az.nrep - 1)]; },
           [&](int k, int) { return line[4 * k + fk < az.nodd ? Kz + 4 * k + fk : 0]; });
       const int l = 16 * t + fr, m = refl(l, az);
@@ -613,7 +620,7 @@ constexpr size_t PLANE_BYTES = 48 * 48 * 8;
 // Smallest pitches >= len at which a fragment read meets no bank twice: 16 rows x 4
 // consecutive values (FP64: 2 at a time), or 4 (2) rows x 16 values.
 inline int pitch_rows(int len, int elem) {
-  return elem == 8 ? (len - 2 + 31) / 32 * 32 + 2 : (len - 4 + 63) / 64 * 64 + 4;
+  return elem == 8 ? (len - 2 + 31) / 32 * 32 + 2 : (len - 34 + 63) / 64 * 64 + 34;
 }
 inline int pitch_cols(int len, int elem) {
   return elem == 8 ? (len - 16 + 31) / 32 * 32 + 16 : (len - 16 + 63) / 64 * 64 + 16;
@@ -631,10 +638,10 @@ hipError_t launch(K kernel, const StripArgs& g, long blocks, int waves, size_t l
 }
 
 // Lines of a strip (1 or 2 times 16) for P groups of Q lines: the fewer strips per CU,
-// counting a quarter of a 16-line strip for what does not shrink with it.  FP64 solves
-// with 16 / 32 lines everywhere: 255^3 702 / 653 us, 511^3 8892 / 8295, but
-// (59, 449, 449) 665 / 734, (449, 59, 59) 77 / 103 (too few strips); this rule takes the
-// faster of each.
+// counting a quarter of a 16-line strip for what does not shrink with it.  Solves with
+// 16 / 32 lines everywhere: FP64 255^3 646 / 624 us, 511^3 7945 / 7408, but 95^3 44 / 52,
+// (449, 59, 59) 80 / 110 (too few strips); FP32 255^3 429 / 381, 95^3 36 / 42.  64 lines
+// are no faster (FP32 255^3 379, 511^3 4290 against 4304).
 inline int strip_cols(long P, long Q, size_t line_bytes) {
   auto cost = [&](int c) { return (double)((P * ((Q + 16 * c - 1) / (16 * c)) + 255) / 256) * (c + 0.25); };
   return 32 * line_bytes <= LDS_MAX && cost(2) <= cost(1) ? 2 : 1;
@@ -658,6 +665,7 @@ template <class T, int TT, int OP, bool SPECTRAL>
 static hipError_t col_launch(StripArgs g, hipStream_t s) {
   using namespace stripk;
   const int waves = (g.ax.nrep + 16 * TT - 1) / (16 * TT);
+  g.tiles = strip_tiles(g.ax.nrep);
   const size_t line = (size_t)strip_len(g.ax) * sizeof(T);
   const int tc = strip_cols(g.P, g.Q, line);
   g.ntiles = (g.Q + 16 * tc - 1) / (16 * tc) * g.P;
@@ -688,6 +696,7 @@ template <class T, class TI, int TT, int OP>
 static hipError_t row_launch(StripArgs g, hipStream_t s) {
   using namespace stripk;
   const int waves = (g.ax.nrep + 16 * TT - 1) / (16 * TT);
+  g.tiles = strip_tiles(g.ax.nrep);
   g.stride = pitch_rows(strip_len(g.ax), sizeof(T));
   const size_t line = (size_t)g.stride * sizeof(T);
   const int tc = strip_cols(1, g.P, line);
@@ -716,6 +725,8 @@ hipError_t launch_strip_plane(StripArgs g, int op, hipStream_t s) {
   using namespace stripk;
   if (!strip_plane_ok(g.ay, g.ax, sizeof(T)) || g.P < 1 || g.ldx < g.ax.n || (op == STRIP_BWD && g.ldx != g.ax.n))
     return hipErrorInvalidValue;
+  g.tiles = strip_tiles(g.ax.nrep);
+  g.tiles2 = strip_tiles(g.ay.nrep);
   g.stride = pitch_rows(strip_len(g.ax), sizeof(T));
   g.stride2 = pitch_cols(pad16(g.ax.n), sizeof(T));
   const size_t lds = (size_t)pad16(g.ay.n) * (g.stride + g.stride2) * sizeof(T);

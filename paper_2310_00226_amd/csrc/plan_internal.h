@@ -32,6 +32,7 @@ struct sem_plan {
   double* d_gff[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
   double* d_gbf[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
   int fld[3] = {0, 0, 0};
+  double* d_gst[3] = {nullptr, nullptr, nullptr};  // the same blocks in strip order (strip_pack_axis)
   double* d_lamf64[3] = {nullptr, nullptr, nullptr};  // eigenvalues in folded mode order (FP64 path)
   // low-precision factors (created on first use): [axis][0 = forward, 1 = backward],
   // layout [l][k], zero-padded to lp_ld x lp_ld
@@ -49,9 +50,7 @@ struct sem_plan {
   int lpf_frow2[3] = {0, 0, 0};
   long lpf_plane[3] = {0, 0, 0};
   double* d_lamf[3] = {nullptr, nullptr, nullptr};  // eigenvalues in folded mode order
-  // FP32 strip factors [axis][forward symmetric, antisymmetric, backward symmetric,
-  // antisymmetric], the layout of d_gff / d_gbf (pitch fld); one allocation per axis
-  float* lps[3][4] = {};
+  float* lps[3] = {};  // FP32 strip factors of each axis (strip_pack_axis)
   int lp_ready = 0;
   // tuned launch shapes per precision (index sem_prec) and pass: FP32 tile rows,
   // BF16 tile order group (lp_tune)

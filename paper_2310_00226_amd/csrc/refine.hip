@@ -128,9 +128,9 @@ void release_lowp(sem_plan* p) {
       (void)hipFree(p->lpf[a][d]);
       p->lp_f32[a][d] = p->lp_hi[a][d] = p->lp_lo[a][d] = p->lpf[a][d] = nullptr;
     }
-  for (auto& axis : p->lps) {
-    (void)hipFree(axis[0]);
-    for (float*& g : axis) g = nullptr;
+  for (float*& g : p->lps) {
+    (void)hipFree(g);
+    g = nullptr;
   }
   for (int a = 0; a < 3; ++a) {
     (void)hipFree(p->d_lamf[a]);
@@ -206,26 +206,15 @@ static sem_status ensure_lowp(sem_plan* p) {
         return hip_fail(e, "folded factor upload");
       }
     }
-    // strip factors: G[m][l] = A[l][m], as the FP64 ones, four blocks in one allocation
-    {
-      const int fld = p->fld[a];
-      const size_t block = (size_t)(fld + 128) * fld;
-      std::vector<float> g(4 * block, 0.0f);
-      for (int i = 0; i < 4; ++i) {
-        const int rows = i == 1 ? no : nr, cols = i == 3 ? no : nr;
-        for (int l = 0; l < rows; ++l)
-          for (int m = 0; m < cols; ++m)
-            g[i * block + (size_t)m * fld + l] = (float)(i < 2 ? ax.ffold[(size_t)(l + i * nr) * nr + m]
-                                                        : i == 2 ? ax.bfold_sym[(size_t)l * nr + m]
-                                                                 : ax.bfold_anti[(size_t)l * no + m]);
-      }
+    if (strip_axis_ok(StripAxis{n, nr, no, 0}, sizeof(float))) {
+      std::vector<float> g(4 * strip_pack_elems<float>(nr), 0.0f);
+      strip_pack_axis(ax.ffold.data(), ax.bfold_sym.data(), ax.bfold_anti.data(), nr, no, g.data());
       hipError_t e;
-      if ((e = hipMalloc(&p->lps[a][0], g.size() * 4)) != hipSuccess ||
-          (e = hipMemcpy(p->lps[a][0], g.data(), g.size() * 4, hipMemcpyHostToDevice)) != hipSuccess) {
+      if ((e = hipMalloc(&p->lps[a], g.size() * 4)) != hipSuccess ||
+          (e = hipMemcpy(p->lps[a], g.data(), g.size() * 4, hipMemcpyHostToDevice)) != hipSuccess) {
         release_lowp(p);
         return hip_fail(e, "strip factor upload");
       }
-      for (int i = 1; i < 4; ++i) p->lps[a][i] = p->lps[a][0] + i * block;
     }
     hipError_t e;
     if ((e = hipMalloc(&p->d_lamf[a], sizeof(double) * n)) != hipSuccess ||
@@ -404,6 +393,16 @@ static StripAxis strip_axis(const sem_plan* p, int a) {
   return StripAxis{p->dims[a], p->ax[a].nrep, p->ax[a].nodd, p->bc[a] == SEM_BC_PERIODIC ? 1 : 0};
 }
 
+// The four packed factors of an axis.
+template <class T>
+static void strip_factors(const T* g, int nrep, const void** fs, const void** fa, const void** bs, const void** ba) {
+  const size_t block = strip_pack_elems<T>(nrep);
+  *fs = g;
+  *fa = g + block;
+  *bs = g + 2 * block;
+  *ba = g + 3 * block;
+}
+
 // Whether the FP32 products of a plan run on strips (every axis up to 1024 nodes).
 static bool f32_strips(const sem_plan* p) {
   for (int a = 0; a < 3; ++a)
@@ -420,11 +419,7 @@ static hipError_t f32_strip_fd(sem_plan* p, const LpWork& w, const Spectral& sp,
     StripArgs g;
     g.x = x;
     g.y = y;
-    g.fs = p->lps[a][0];
-    g.fa = p->lps[a][1];
-    g.bs = p->lps[a][2];
-    g.ba = p->lps[a][3];
-    g.ldg = p->fld[a];
+    strip_factors(p->lps[a], p->ax[a].nrep, &g.fs, &g.fa, &g.bs, &g.ba);
     g.ax = strip_axis(p, a);
     g.P = P;
     g.Q = Q;
@@ -449,11 +444,7 @@ static hipError_t f32_strip_fd(sem_plan* p, const LpWork& w, const Spectral& sp,
   if (plane) {
     for (StripArgs* g : {&in, &out}) {
       g->ay = strip_axis(p, 1);
-      g->fs2 = p->lps[1][0];
-      g->fa2 = p->lps[1][1];
-      g->bs2 = p->lps[1][2];
-      g->ba2 = p->lps[1][3];
-      g->ldg2 = p->fld[1];
+      strip_factors(p->lps[1], p->ax[1].nrep, &g->fs2, &g->fa2, &g->bs2, &g->ba2);
     }
     e = f64_src ? launch_strip_plane<float, double>(in, STRIP_FWD, s)
                 : launch_strip_plane<float, float>(in, STRIP_FWD, s);
@@ -711,11 +702,7 @@ hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, dou
     StripArgs g;
     g.x = x;
     g.y = y;
-    g.fs = p->d_gff[a][0];
-    g.fa = p->d_gff[a][1];
-    g.bs = p->d_gbf[a][0];
-    g.ba = p->d_gbf[a][1];
-    g.ldg = p->fld[a];
+    strip_factors(p->d_gst[a], r[a], &g.fs, &g.fa, &g.bs, &g.ba);
     g.ax = ax[a];
     g.P = P;
     g.Q = Q;
@@ -727,11 +714,7 @@ hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, dou
   auto plane_args = [&](const double* x, double* y) {
     StripArgs g = strip_args(2, x, y, nx, 1);
     g.ay = ax[1];
-    g.fs2 = p->d_gff[1][0];
-    g.fa2 = p->d_gff[1][1];
-    g.bs2 = p->d_gbf[1][0];
-    g.ba2 = p->d_gbf[1][1];
-    g.ldg2 = p->fld[1];
+    strip_factors(p->d_gst[1], r[1], &g.fs2, &g.fa2, &g.bs2, &g.ba2);
     return g;
   };
   if (plane) {  // z and y forward: f -> tmp

@@ -96,6 +96,12 @@ static hipError_t upload_fold_factors(sem_plan* p, int a) {
     if ((e = hipMemcpy(*dst[i], g[i].data(), sizeof(double) * g[i].size(), hipMemcpyHostToDevice)) != hipSuccess)
       return e;
   }
+  if (strip_axis_ok(StripAxis{ax.n, nr, no, 0}, sizeof(double))) {
+    std::vector<double> st(4 * strip_pack_elems<double>(nr), 0.0);
+    strip_pack_axis(ax.ffold.data(), ax.bfold_sym.data(), ax.bfold_anti.data(), nr, no, st.data());
+    const hipError_t e = upload_vec(st, &p->d_gst[a]);
+    if (e != hipSuccess) return e;
+  }
   return upload_vec(ax.lam_fold, &p->d_lamf64[a]);
 }
 
@@ -285,6 +291,7 @@ void sem_plan_destroy(sem_plan* p) {
     (void)hipFree(p->d_hb[a]);
     (void)hipFree(p->d_mass[a]);
     (void)hipFree(p->d_lamf64[a]);
+    (void)hipFree(p->d_gst[a]);
     for (int b = 0; b < 2; ++b) {
       (void)hipFree(p->d_gff[a][b]);
       (void)hipFree(p->d_gbf[a][b]);
