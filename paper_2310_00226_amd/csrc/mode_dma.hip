@@ -14,7 +14,8 @@
 //    16-byte chunks placed at slot chunk ^ g(row), g(row) = ((row>>1)^(row>>2))&3,
 //    which makes the fragment reads (16 rows x one chunk per 16 lanes)
 //    bank-conflict-free for 32 and 64 four-byte banks;
-//  * block tile 256 (l) x 256 (p), eight waves of 128 x 64;
+//  * block tile 256 (l) x 256 (p) of eight waves of 128 x 64, or, where it would pad
+//    more than it saves (dma_cost), 128 x 128 or 64 x 128 of four waves;
 //  * the output columns run over the padded output layout, p = a * ldy + b with
 //    b < ldy, so that an output row (fixed l) of the tile is one contiguous
 //    segment y[l * A * ldy + p] (padding columns b >= B receive finite values
@@ -75,13 +76,30 @@ typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int BM = 256, BN = 256, WL = 2, WP = 4;
-constexpr int NTHREADS = 64 * WL * WP;  // 512
-constexpr int TL = BM / WL, TP = BN / WP;  // 128 x 64 per wave
-constexpr int FL = TL / 16, FP = TP / 16;  // 8 x 4 MFMA tiles
-constexpr int BK = 32;                      // BF16 elements per chunk (64-byte LDS rows)
-constexpr int ROWB = BK * 2;                // bytes per LDS row
-constexpr int TILEB = BM * ROWB;            // bytes per operand tile (16 KB)
+constexpr int BK = 32;        // BF16 elements per chunk (64-byte LDS rows)
+constexpr int ROWB = BK * 2;  // bytes per LDS row
+
+// Block tile BM (l) x BN (p) on WL x WP waves.
+template <int BM_, int BN_, int WL_, int WP_>
+struct Tile {
+  static constexpr int BM = BM_, BN = BN_, WL = WL_, WP = WP_;
+  static constexpr int NTHREADS = 64 * WL * WP;
+  static constexpr int TL = BM / WL, TP = BN / WP;      // wave tile
+  static constexpr int FL = TL / 16, FP = TP / 16;      // MFMA tiles per wave
+  static constexpr int FB = BM * ROWB, XB = BN * ROWB;  // bytes of a factor / tensor tile
+  // DMA instructions of a wave per operand tile: each 1 KB instruction fills 16 rows
+  static constexpr int QF = BM / 16 / (WL * WP), QX = BN / 16 / (WL * WP);
+  static_assert(QF * 16 * WL * WP == BM && QX * 16 * WL * WP == BN, "whole DMA instructions per wave");
+  // epilogue staging: BF16 rows of BN + 16 elements, FP32 rows of BN + 8: row starts 8
+  // banks apart, so the 16 rows x 4 column groups of one 8-byte (16-byte) write
+  // instruction meet at most two to a bank
+  static constexpr int EROW_H = BN + 16, EROW_F = BN + 8;
+  static constexpr int EPIB = BM * EROW_H * 2;
+  static_assert(TL * EROW_F * 4 <= EPIB, "FP32 staging fits");
+};
+typedef Tile<256, 256, 2, 4> T256;  // 8 waves of 128 x 64
+typedef Tile<128, 128, 2, 2> T128;  // 4 waves of 64 x 64
+typedef Tile<64, 128, 2, 2> T64;    // 4 waves of 32 x 64
 
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ (row >> 2)) & 3; }
 
@@ -125,30 +143,24 @@ __device__ __forceinline__ long in_col(long bo, const DmaArgs& g) {
   return min(bo, (long)g.B - 1);
 }
 
-// epilogue staging: BF16 rows of 272 elements, FP32 rows of 264: row starts 8
-// banks apart, so the 16 rows x 4 column groups of one 8-byte (16-byte) write
-// instruction meet at most two to a bank
-constexpr int EROW_H = 272, EROW_F = 264;
-constexpr int EPIB = 256 * EROW_H * 2;  // 256 BF16 rows (>= 128 FP32 rows)
-static_assert(128 * EROW_F * 4 <= EPIB, "FP32 staging fits");
-
-template <int MODE>
+template <int MODE, class G>
 struct KCfg {
   static constexpr int NS = MODE == LP_BF16X3 ? 2 : 1;
   static constexpr int STAGES = NS == 2 ? 2 : 4;
-  static constexpr int STAGEB = NS * 2 * TILEB;  // factor + tensor tiles, all planes
-  // DMA instructions per chunk per wave: each 1 KB instruction fills 16 rows
-  static constexpr int DMA_PER_TILE = BM / 16 / (WL * WP);  // 2
-  static constexpr int D = NS * 2 * DMA_PER_TILE;
-  static constexpr int SMEM = STAGES * STAGEB > EPIB ? STAGES * STAGEB : EPIB;
+  static constexpr int PLANEB = G::FB + G::XB;   // factor + tensor tile of one plane
+  static constexpr int STAGEB = NS * PLANEB;
+  static constexpr int D = NS * (G::QF + G::QX);  // DMA instructions per chunk per wave
+  static constexpr int SMEM = STAGES * STAGEB > G::EPIB ? STAGES * STAGEB : G::EPIB;
 };
 
-// One 256 x 256 output tile t of a pass: DMA ring over the contraction, MFMAs,
+// One output tile t of a pass: DMA ring over the contraction, MFMAs,
 // epilogue.  Every thread of the block calls it with the same t.
-template <int MODE, class TOut, int EPI, int COL>
+template <int MODE, class TOut, int EPI, int COL, class G>
 __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigned char* const smem) {
-  typedef KCfg<MODE> C;
+  typedef KCfg<MODE, G> C;
   constexpr int NS = C::NS, S = C::STAGES;
+  constexpr int BM = G::BM, BN = G::BN, WP = G::WP, TL = G::TL, TP = G::TP, FL = G::FL, FP = G::FP;
+  constexpr int NTHREADS = G::NTHREADS, QF = G::QF, QX = G::QX, EROW_H = G::EROW_H, EROW_F = G::EROW_F;
   unsigned char* const st0 = smem;
   unsigned char* const st1 = smem + C::STAGEB;
   unsigned char* const st2 = smem + (S > 2 ? 2 : 0) * C::STAGEB;
@@ -170,13 +182,13 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
   const int lrows = (int)min((long)BM, (long)(blk2 ? g.L2 : g.L1) - lb * BM);  // valid rows of the tile
   const int orow0 = (blk2 ? g.L1 : 0) + (int)(lb * BM);
   const long Pp = (long)g.A * g.ldy;  // padded output columns
-  // COL_FOLD: tile pt = (a, block of 128 representatives); else 256 consecutive
+  // COL_FOLD: tile pt = (a, block of BN / 2 representatives); else BN consecutive
   // padded output columns
   long fa = 0, fr0 = 0, p0 = 0;
   if constexpr (COL == COL_FOLD) {
-    const long tpa = (g.bsym + 127) / 128;
+    const long tpa = (g.bsym + BN / 2 - 1) / (BN / 2);
     fa = pt / tpa;
-    fr0 = (pt - fa * tpa) * 128;
+    fr0 = (pt - fa * tpa) * (BN / 2);
   } else {
     p0 = pt * BN;
   }
@@ -188,19 +200,23 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
   const int nchunk = (K + BK - 1) / BK;
 
   // ---- DMA source addresses --------------------------------------------------
-  // Instruction q (0, 1) of this wave fills tile rows 16*(2*wave + q) .. +15;
-  // lane i writes LDS slot i % 4 of row 16*(2*wave + q) + i / 4 and therefore
-  // fetches chunk (i % 4) ^ g(row) of that row.  Output columns map to input rows
-  // (a, b) as described above; padding columns and columns past the end read a
-  // valid row instead.
-  const unsigned short* fsrc[2];
-  const unsigned short* xsrc[2];
-  int fchunk[2];
+  // Instruction q of this wave fills 16 tile rows from 16 (Q wave + q); lane i writes
+  // LDS slot i % 4 of row i / 4 of them and therefore fetches chunk (i % 4) ^ g(row) of
+  // that row.  Output columns map to input rows (a, b) as described above; padding
+  // columns and columns past the end read a valid row instead.
+  const unsigned short* fsrc[QF];
+  const unsigned short* xsrc[QX];
+  int fchunk[QF], xchunk[QX];  // element offset of the chunk
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int row = 16 * (2 * wave + q) + lane / 4;
-    fchunk[q] = ((lane & 3) ^ swz(row)) * 8;  // element offset of the chunk
+  for (int q = 0; q < QF; ++q) {
+    const int row = 16 * (QF * wave + q) + lane / 4;
+    fchunk[q] = ((lane & 3) ^ swz(row)) * 8;
     fsrc[q] = g.f + (size_t)(frow0 + row) * g.ldf;
+  }
+#pragma unroll
+  for (int q = 0; q < QX; ++q) {
+    const int row = 16 * (QX * wave + q) + lane / 4;
+    xchunk[q] = ((lane & 3) ^ swz(row)) * 8;
     long pr = g.P - 1;
     if constexpr (COL == COL_FOLD) {
       const int r = (int)min(fr0 + (row >> 1), (long)g.bsym - 1);
@@ -219,19 +235,22 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
   auto issue = [&](unsigned char* stage, int c) {
     const int k0 = c * BK;
 #pragma unroll
-    for (int pl = 0; pl < NS; ++pl)
+    for (int pl = 0; pl < NS; ++pl) {
+      // factor: padded, always in bounds; tensor: chunks past the row pitch
+      // are redirected to the block start (finite data times zero factor columns)
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int ldsrow = 16 * (2 * wave + q);
-        unsigned char* fdst = stage + pl * 2 * TILEB + ldsrow * ROWB;
-        unsigned char* xdst = stage + pl * 2 * TILEB + TILEB + ldsrow * ROWB;
-        // factor: padded, always in bounds; tensor: chunks past the row pitch
-        // are redirected to the block start (finite data times zero factor columns)
-        const int kf = k0 + fchunk[q];
+      for (int q = 0; q < QF; ++q)
+        __builtin_amdgcn_global_load_lds((const void*)(fsrc[q] + pl * g.fplane + k0 + fchunk[q]),
+                                         (lds_void*)(stage + pl * C::PLANEB + 16 * (QF * wave + q) * ROWB), 16, 0, 0);
+#pragma unroll
+      for (int q = 0; q < QX; ++q) {
+        const int kf = k0 + xchunk[q];
         const int kx = koff + kf < g.ldx ? kf : 0;
-        __builtin_amdgcn_global_load_lds((const void*)(fsrc[q] + pl * g.fplane + kf), (lds_void*)fdst, 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((const void*)(xsrc[q] + pl * g.xplane + kx), (lds_void*)xdst, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((const void*)(xsrc[q] + pl * g.xplane + kx),
+                                         (lds_void*)(stage + pl * C::PLANEB + G::FB + 16 * (QX * wave + q) * ROWB), 16,
+                                         0, 0);
       }
+    }
   };
 
   f4_t acc[FL][FP];
@@ -266,13 +285,13 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
       bf8_t bh[FP], bl[FP];
 #pragma unroll
       for (int j = 0; j < FP; ++j) {
-        bh[j] = *reinterpret_cast<const bf8_t*>(stage + TILEB + boff[j]);
-        bl[j] = *reinterpret_cast<const bf8_t*>(stage + 3 * TILEB + boff[j]);
+        bh[j] = *reinterpret_cast<const bf8_t*>(stage + G::FB + boff[j]);
+        bl[j] = *reinterpret_cast<const bf8_t*>(stage + C::PLANEB + G::FB + boff[j]);
       }
 #pragma unroll
       for (int i = 0; i < FL; ++i) {
         const bf8_t ah = *reinterpret_cast<const bf8_t*>(stage + aoff[i]);
-        const bf8_t al = *reinterpret_cast<const bf8_t*>(stage + 2 * TILEB + aoff[i]);
+        const bf8_t al = *reinterpret_cast<const bf8_t*>(stage + C::PLANEB + aoff[i]);
 #pragma unroll
         for (int j = 0; j < FP; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], al, acc[i][j], 0, 0, 0);
 #pragma unroll
@@ -287,7 +306,7 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
 #pragma unroll
       for (int i = 0; i < FL; ++i) a[i] = *reinterpret_cast<const bf8_t*>(stage + aoff[i]);
 #pragma unroll
-      for (int j = 0; j < FP; ++j) b[j] = *reinterpret_cast<const bf8_t*>(stage + TILEB + boff[j]);
+      for (int j = 0; j < FP; ++j) b[j] = *reinterpret_cast<const bf8_t*>(stage + G::FB + boff[j]);
       __builtin_amdgcn_sched_barrier(0);  // all fragment reads in flight before the first MFMA
 #pragma unroll
       for (int i = 0; i < FL; ++i)
@@ -338,11 +357,11 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
   const int pl0 = wn + 4 * fg;  // first of the lane's columns in each 16-column block
   __syncthreads();              // every wave is done with the ring
   if constexpr (sizeof(TOut) == 4) {
-    // FP32 output, plain columns: two rounds of 128 rows
+    // FP32 output, plain columns: a round for each row of waves
     float* sf = reinterpret_cast<float*>(smem);
     float* __restrict__ yp = reinterpret_cast<float*>(g.y);
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+    for (int half = 0; half < G::WL; ++half) {
       if (half) __syncthreads();  // the previous round's readers are done
       if (wm == half * TL) {
 #pragma unroll
@@ -371,6 +390,7 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
       // both into LDS behind the staging area
       float* const dcol = reinterpret_cast<float*>(smem + C::SMEM);
       float* const drow = dcol + BN;
+      static_assert(NTHREADS >= BN + BM, "a thread per column and row of the tile");
       if (tid < BN) {
         const long c = p0 + tid;
         float v = 0.0f;
@@ -380,7 +400,7 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
           v = (float)(g.epi.l1[a] + g.epi.l2[in_col(bo, g)]);
         }
         dcol[tid] = v;
-      } else {
+      } else if (tid < BN + BM) {
         const int lr = tid - BN;
         drow[lr] = (float)g.epi.l0[orow0 + (lr < lrows ? lr : lrows - 1)];
       }
@@ -441,7 +461,7 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
           }
           unsigned short* srow = sh + (16 * i + fr + wm) * EROW_H;
           if constexpr (COL == COL_FOLD) {
-            // v+ of orbits c/2, c/2 + 1 to staging columns c/2.., v- to 128 + c/2..
+            // v+ of orbits c/2, c/2 + 1 to staging columns c/2.., v- to BN / 2 + c/2..
             const int sc = (pl0 + 16 * j) >> 1;
             *reinterpret_cast<unsigned*>(srow + sc) = w[0];
             *reinterpret_cast<unsigned*>(srow + BN / 2 + sc) = w[1];
@@ -458,10 +478,10 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
         if (row >= lrows) continue;
         const size_t ybase = (size_t)(orow0 + row) * Pp;
         if constexpr (COL == COL_FOLD) {
-          // chunk ch < 16: v+ columns fr0 + 8 ch; else v- columns bpad + fr0 + 8 (ch - 16)
-          const long rc = fr0 + 8 * (ch & 15);
+          // chunk ch < BN / 16: v+ columns fr0 + 8 ch; else v- columns bpad + fr0 + 8 (ch - BN / 16)
+          const long rc = fr0 + 8 * (ch & (BN / 16 - 1));
           if (rc < g.bpad)  // bpad is a multiple of 32: a chunk is wholly in or out
-            *reinterpret_cast<u4_t*>(yp + ybase + fa * g.ldy + (ch >= 16 ? g.bpad : 0) + rc) =
+            *reinterpret_cast<u4_t*>(yp + ybase + fa * g.ldy + (ch >= BN / 16 ? g.bpad : 0) + rc) =
                 *reinterpret_cast<const u4_t*>(sh + row * EROW_H + 8 * ch);
         } else {
           const long pc = p0 + 8 * ch;
@@ -473,28 +493,28 @@ __device__ __forceinline__ void dma_tile(const DmaArgs& g, const long t, unsigne
   }
 }
 
-// A pass: one block per tile (persist = 0, blocks numbered XCD-aware), or one
-// block per CU looping over tiles (persist = 1): each XCD takes a contiguous range
+// A pass: one block per tile (persist = 0, blocks numbered XCD-aware), or as many
+// blocks as fit the CUs looping over tiles (persist = 1): each XCD takes a contiguous range
 // of the tile numbering and its blocks stride through it, so that the stores of
 // one tile drain while the next tile's first chunks stream in.
-template <int MODE, class TOut, int EPI, int COL>
-__global__ __launch_bounds__(NTHREADS) void mode_rot_dma(DmaArgs g) {
-  typedef KCfg<MODE> C;
-  // DIVIDE keeps the tile's 256 column and 256 row parts of the denominators
+template <int MODE, class TOut, int EPI, int COL, class G>
+__global__ __launch_bounds__(G::NTHREADS) void mode_rot_dma(DmaArgs g) {
+  typedef KCfg<MODE, G> C;
+  // DIVIDE keeps the tile's column and row parts of the denominators
   // behind the staging area
-  constexpr int SMEM_ALL = C::SMEM + (EPI == EPI_DIVIDE ? 2 * 256 * 4 : 0);
+  constexpr int SMEM_ALL = C::SMEM + (EPI == EPI_DIVIDE ? (G::BM + G::BN) * 4 : 0);
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM_ALL];
   if (!g.persist) {
     const long t = xcd_tile(g.nbp);
     if (t >= g.ntiles) return;  // whole block leaves together, before any barrier
-    dma_tile<MODE, TOut, EPI, COL>(g, t, smem);
+    dma_tile<MODE, TOut, EPI, COL, G>(g, t, smem);
     return;
   }
   const long xcd = blockIdx.x & 7, j = blockIdx.x >> 3, nper = gridDim.x >> 3;
   const long per = (g.ntiles + 7) / 8;
   const long t_end = min((xcd + 1) * per, g.ntiles);
   for (long t = xcd * per + j; t < t_end; t += nper) {  // uniform over the block
-    dma_tile<MODE, TOut, EPI, COL>(g, t, smem);
+    dma_tile<MODE, TOut, EPI, COL, G>(g, t, smem);
     __syncthreads();  // the next tile's DMAs overwrite the staging area
   }
 }
@@ -787,9 +807,10 @@ bool dma_supported(const LpPass& ps) {
   return false;
 }
 
-template <int MODE, class TOut, int EPI, int COL>
-static hipError_t launch_dma_t(const LpPass& ps, hipStream_t stream) {
+template <int MODE, class TOut, int EPI, int COL, class G>
+static hipError_t launch_dma_g(const LpPass& ps, hipStream_t stream) {
   using namespace dmak;
+  constexpr int BM = G::BM, BN = G::BN;
   DmaArgs g;
   g.x = (const unsigned short*)ps.x;
   g.xplane = ps.xplane;
@@ -815,12 +836,8 @@ static hipError_t launch_dma_t(const LpPass& ps, hipStream_t stream) {
   g.bn = ps.bn;
   g.bper = ps.bper;
   g.epi = ps.epi;
-  g.tl1 = (ps.L + BM - 1) / BM;
-  g.tiles_l = g.tl1 + (ps.K2 > 0 ? (ps.L2 + BM - 1) / BM : 0);
-  const long tiles_p =
-      COL == COL_FOLD ? (long)ps.A * ((ps.bsym + 127) / 128) : ((long)ps.A * ps.ldy + BN - 1) / BN;
-  g.tiles_p = tiles_p;
-  g.ntiles = g.tiles_l * tiles_p;
+  dma_tiles<G, COL>(ps, &g.tl1, &g.tiles_l, &g.tiles_p);
+  g.ntiles = g.tiles_l * g.tiles_p;
   // tile_group: g in {1, 2, 4} (one block per tile) or DMA_PERSIST + g (one block
   // per CU looping over the tiles)
   const int tg = ps.tile_group >= 1 ? ps.tile_group : 1;
@@ -835,11 +852,45 @@ static hipError_t launch_dma_t(const LpPass& ps, hipStream_t stream) {
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    const long full = (long)(cus > 8 ? cus : 8) / 8 * 8;  // one block per CU, every XCD alike
+    // as many blocks as fit a CU, every XCD alike
+    const long per_cu = 160 * 1024 / (KCfg<MODE, G>::SMEM + (EPI == EPI_DIVIDE ? (BM + BN) * 4 : 0));
+    const long full = (long)(cus > 8 ? cus : 8) / 8 * 8 * per_cu;
     grid = full < g.nbp ? full : g.nbp;
   }
-  mode_rot_dma<MODE, TOut, EPI, COL><<<dim3((unsigned)grid), dim3(NTHREADS), 0, stream>>>(g);
+  mode_rot_dma<MODE, TOut, EPI, COL, G><<<dim3((unsigned)grid), dim3(G::NTHREADS), 0, stream>>>(g);
   return hipGetLastError();
+}
+
+// Tiles of a pass along l (both blocks) and p.
+template <class G, int COL>
+static void dma_tiles(const LpPass& ps, long* tl1, long* tiles_l, long* tiles_p) {
+  *tl1 = (ps.L + G::BM - 1) / G::BM;
+  *tiles_l = *tl1 + (ps.K2 > 0 ? (ps.L2 + G::BM - 1) / G::BM : 0);
+  *tiles_p = COL == COL_FOLD ? (long)ps.A * ((ps.bsym + G::BN / 2 - 1) / (G::BN / 2))
+                             : ((long)ps.A * ps.ldy + G::BN - 1) / G::BN;
+}
+
+// Which block tile: the most tiles that a CU gets times the tile's area times its
+// measured weight (a 128 x 128 tile takes 1.2 times its share of a 256 x 256 tile's
+// time where nothing is padded, n = 511; a 64 x 128 one 1.35 times).  The large tile
+// pads 60 .. 150 modes or orbits to 256 and leaves CUs idle: six split-BF16 passes with
+// the 256 / 128 / 64-row tile everywhere: 119^3 92 / 49 / 41 us, 191^3 210 / 118 / 113,
+// (257, 311, 227) 435 / 300 / 277, 299^3 516 / 469 / 406, 511^3 1784 / 2041 / 2204.
+// Every output element is summed in the same order by all three.
+template <class G, int COL>
+static long dma_cost(const LpPass& ps, long weight) {
+  long tl1, tiles_l, tiles_p;
+  dma_tiles<G, COL>(ps, &tl1, &tiles_l, &tiles_p);
+  return (tiles_l * tiles_p + 255) / 256 * (G::BM * G::BN / 8192) * weight;
+}
+
+template <int MODE, class TOut, int EPI, int COL>
+static hipError_t launch_dma_t(const LpPass& ps, hipStream_t stream) {
+  using namespace dmak;
+  const long c256 = dma_cost<T256, COL>(ps, 20), c128 = dma_cost<T128, COL>(ps, 24), c64 = dma_cost<T64, COL>(ps, 27);
+  if (c256 <= c128 && c256 <= c64) return launch_dma_g<MODE, TOut, EPI, COL, T256>(ps, stream);
+  if (c128 <= c64) return launch_dma_g<MODE, TOut, EPI, COL, T128>(ps, stream);
+  return launch_dma_g<MODE, TOut, EPI, COL, T64>(ps, stream);
 }
 
 template <int MODE>
