@@ -807,6 +807,15 @@ bool dma_supported(const LpPass& ps) {
   return false;
 }
 
+// Tiles of a pass along l (both blocks) and p.
+template <class G, int COL>
+static void dma_tiles(const LpPass& ps, long* tl1, long* tiles_l, long* tiles_p) {
+  *tl1 = (ps.L + G::BM - 1) / G::BM;
+  *tiles_l = *tl1 + (ps.K2 > 0 ? (ps.L2 + G::BM - 1) / G::BM : 0);
+  *tiles_p = COL == COL_FOLD ? (long)ps.A * ((ps.bsym + G::BN / 2 - 1) / (G::BN / 2))
+                             : ((long)ps.A * ps.ldy + G::BN - 1) / G::BN;
+}
+
 template <int MODE, class TOut, int EPI, int COL, class G>
 static hipError_t launch_dma_g(const LpPass& ps, hipStream_t stream) {
   using namespace dmak;
@@ -859,15 +868,6 @@ static hipError_t launch_dma_g(const LpPass& ps, hipStream_t stream) {
   }
   mode_rot_dma<MODE, TOut, EPI, COL, G><<<dim3((unsigned)grid), dim3(G::NTHREADS), 0, stream>>>(g);
   return hipGetLastError();
-}
-
-// Tiles of a pass along l (both blocks) and p.
-template <class G, int COL>
-static void dma_tiles(const LpPass& ps, long* tl1, long* tiles_l, long* tiles_p) {
-  *tl1 = (ps.L + G::BM - 1) / G::BM;
-  *tiles_l = *tl1 + (ps.K2 > 0 ? (ps.L2 + G::BM - 1) / G::BM : 0);
-  *tiles_p = COL == COL_FOLD ? (long)ps.A * ((ps.bsym + G::BN / 2 - 1) / (G::BN / 2))
-                             : ((long)ps.A * ps.ldy + G::BN - 1) / G::BN;
 }
 
 // Which block tile: the most tiles that a CU gets times the tile's area times its
