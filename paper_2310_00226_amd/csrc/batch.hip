@@ -106,7 +106,7 @@ struct sem_batch {
   std::vector<LpDesc> h_desc;
   std::vector<ResDesc> h_rdesc;
   std::vector<Group> groups;
-  std::vector<Group> rgroups;  // residual groups: var = k
+  std::vector<Group> rgroups;  // residual groups: var = k, tile_rows = rows of y per wave
   hipStream_t side[NSIDE] = {nullptr, nullptr, nullptr};
   hipEvent_t ev_start = nullptr;
   hipEvent_t ev_side[NSIDE] = {nullptr, nullptr, nullptr};
@@ -179,7 +179,7 @@ int tile_for(const sem_batch* b, int L) {
 }
 
 // Build all pass descriptors (grouped by variant and tile shape) and the residual
-// descriptors (grouped by k) for one solve call.
+// descriptors (grouped by k and rows per wave) for one solve call.
 // Solves with skip[i] set run outside the persistent launches and get no descriptor.
 sem_status build_descs(sem_batch* b, const double* const* f, double* const* u, const std::vector<char>& skip) {
   b->h_desc.clear();
@@ -201,8 +201,9 @@ sem_status build_descs(sem_batch* b, const double* const* f, double* const* u, c
     }
   b->h_rdesc.clear();
   b->rgroups.clear();
-  for (int k = 1; k <= 8; ++k) {
-    Group g{k, 0, (int)b->h_rdesc.size(), 0, 0};
+  for (int kr = 2; kr < 18; ++kr) {
+    const int k = kr / 2, rows = 1 + kr % 2;
+    Group g{k, rows, (int)b->h_rdesc.size(), 0, 0};
     for (int i = 0; i < b->count; ++i) {
       sem_plan* p = b->plans[i];
       if (p->k != k || skip[i]) continue;
@@ -219,6 +220,7 @@ sem_status build_descs(sem_batch* b, const double* const* f, double* const* u, c
       const double* hb[3] = {p->d_hb[0], p->d_hb[1], p->d_hb[2]};
       ResDesc rd;
       if (!residual_desc(ra, hb, k, p->dims, &rd)) return set_error(SEM_EINVAL, "sem_batch: residual descriptor");
+      if (rd.rows != rows) continue;
       rd.sid = i;
       rd.block0 = g.tiles;
       g.tiles += (long)rd.gx * rd.gy * rd.gz;
@@ -586,7 +588,7 @@ sem_status sem_batch_solve(sem_batch* b, sem_prec prec, double tol, int max_iter
     }
     if (it > 0)
       for (const Group& g : b->rgroups)
-        if ((e = launch_residual_batch(g.var, 1, b->d_rdesc + g.off, g.count, g.tiles, b->d_active, b->stream)) !=
+        if ((e = launch_residual_batch(g.var, g.tile_rows, 1, b->d_rdesc + g.off, g.count, g.tiles, b->d_active, b->stream)) !=
             hipSuccess) {
           drain();
           return hip_fail(e, "sem_batch_solve: residual");

@@ -318,7 +318,7 @@ long residual_march_blocks(const int dims[3], int k);
 hipError_t launch_residual(const ResidualArgs& ra, const double* const hb[3], int k, const int dims[3],
                            hipStream_t stream);
 
-// Residuals of many solves with the same k (1..8) in one launch.  Descriptor i
+// Residuals of many solves with the same k (1..8) and rows in one launch.  Descriptor i
 // (device array, ascending block0) owns blocks [block0, block0 + gx*gy*gz);
 // active: device array of per-solve flags indexed by sid.
 struct ResDesc {
@@ -334,12 +334,13 @@ struct ResDesc {
   int ldr = 0, nx = 0, ny = 0, nz = 0, xchunk = 0, gx = 0, gy = 0, gz = 0;
   int sid = 0;
   double cf = 1.0, cd = 0.0, ch = 1.0;
-  int per = 0;  // bit a set: axis a is periodic (neighbours wrap around)
+  int per = 0;   // bit a set: axis a is periodic (neighbours wrap around)
+  int rows = 2;  // rows of y per wave: launches take descriptors of one kind
 };
 // Fill the geometry and operands of one descriptor (block0 and sid are the
 // caller's); false if k or the arguments are outside what the batch kernel takes.
 bool residual_desc(const ResidualArgs& ra, const double* const hb[3], int k, const int dims[3], ResDesc* d);
-hipError_t launch_residual_batch(int k, int r_kind, const ResDesc* descs, int nd, long total_blocks,
+hipError_t launch_residual_batch(int k, int rows, int r_kind, const ResDesc* descs, int nd, long total_blocks,
                                  const int* active, hipStream_t stream);
 
 }  // namespace semfd

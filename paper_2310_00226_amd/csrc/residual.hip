@@ -16,7 +16,7 @@
 // indices along that axis (the plan's band rows hold the wrap-around couplings).
 //
 // HBM-bound: per node it reads v and f and writes r (24 bytes in FP64).  For
-// k <= 8 a block of 8 waves owns a 16 (y) x 64 (z) column of nodes and marches
+// k <= 8 a block of 8 waves owns a 16 or 8 (y) x 64 (z) column of nodes and marches
 // along x (residual_march_kernel): per x-plane the (16 + 2k) x (64 + 2k) tile of
 // v (core and a halo of k nodes in y and z) is staged in LDS, double-buffered with
 // one barrier per plane (the core from the thread's x-window registers, the halo
@@ -128,13 +128,13 @@ __global__ __launch_bounds__(256) void residual_any_kernel(const double* __restr
 }
 
 // Tiled march: a block (8 waves) owns a TY (y) x TZ (z) column of nodes and marches
-// along x; each wave owns RW rows of y.
-constexpr int RT = 512;                       // threads per block (8 waves)
-constexpr int TY = 16, TZ = 64, RW = TY / 8;  // RW rows of y per wave
-constexpr int RY = TY, RZ = TZ;               // grid granularity
+// along x; each wave owns RW = 1 or 2 rows of y (march_rows), TY = 8 RW.
+constexpr int RT = 512;  // threads per block (8 waves)
+constexpr int TZ = 64;
 
-template <int KH>
+template <int KH, int RW>
 struct TileGeo {
+  static constexpr int TY = 8 * RW;
   static constexpr int ROWS = TY + 2 * KH, COLS = TZ + 2 * KH, PLANE = ROWS * COLS;
   // halo cells of a plane tile: KH rows above and below (full width), KH columns
   // left and right of the core rows
@@ -149,7 +149,7 @@ struct TileGeo {
 // thread's register window of 2 KH + 1 planes, whose front is loaded from global
 // memory one plane ahead.  Out-of-domain values are zero in the tile and the
 // window (their band coefficients are zero as well).
-template <int KH, class TR, bool W>
+template <int KH, class TR, bool W, int RW>
 __device__ __forceinline__ void march_body(const double* __restrict__ v, const double* __restrict__ f,
                                            const double* __restrict__ dg, const double* __restrict__ wt,
                                            TR* __restrict__ r, int ldr, long rplane,
@@ -158,7 +158,8 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
                                            int per, const Coef& c, int bx, int by, int bz,
                                            double* __restrict__ lds, const DotOut& dot = DotOut()) {
   constexpr int BW = 2 * KH + 1;
-  typedef TileGeo<KH> G;
+  typedef TileGeo<KH, RW> G;
+  constexpr int TY = G::TY;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int z0 = bx * TZ, y0 = by * TY;
@@ -313,7 +314,7 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
   }
 }
 
-template <int KH, class TR, bool W>
+template <int KH, class TR, bool W, int RW>
 __global__ __launch_bounds__(RT) void residual_march_kernel(const double* __restrict__ v,
                                                                   const double* __restrict__ f,
                                                                   const double* __restrict__ dg,
@@ -324,8 +325,8 @@ __global__ __launch_bounds__(RT) void residual_march_kernel(const double* __rest
                                                                   const double* __restrict__ hz, int nx, int ny,
                                                                   int nz, int xchunk, int per, Coef c,
                                                                   DotOut dot) {
-  __shared__ double lds[2 * TileGeo<KH>::PLANE + (W ? (2 * KH + 1) * 64 : 0)];
-  march_body<KH, TR, W>(v, f, dg, wt, r, ldr, rplane, hx, hy, hz, nx, ny, nz, xchunk, per, c, blockIdx.x,
+  __shared__ double lds[2 * TileGeo<KH, RW>::PLANE + (W ? (2 * KH + 1) * 64 : 0)];
+  march_body<KH, TR, W, RW>(v, f, dg, wt, r, ldr, rplane, hx, hy, hz, nx, ny, nz, xchunk, per, c, blockIdx.x,
                         blockIdx.y, blockIdx.z, lds, dot);
 }
 
@@ -333,23 +334,23 @@ __global__ __launch_bounds__(RT) void residual_march_kernel(const double* __rest
 // For k = 5 without the weight it fits without spilling (127 instead of 130
 // VGPRs) and runs 10% faster (6.1 vs 6.8 ms at 1000^3); the weighted k = 5
 // march would spill 44 bytes per lane and gain nothing, k = 4 fits either way.
-template <int KH, class TR, bool W>
+template <int KH, class TR, bool W, int RW>
 __global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(4, 8))) void residual_march_kernel_w4(
     const double* __restrict__ v, const double* __restrict__ f, const double* __restrict__ dg,
     const double* __restrict__ wt, TR* __restrict__ r, int ldr, long rplane, const double* __restrict__ hx,
     const double* __restrict__ hy, const double* __restrict__ hz, int nx, int ny, int nz, int xchunk, int per,
     Coef c, DotOut dot) {
-  __shared__ double lds[2 * TileGeo<KH>::PLANE + (W ? (2 * KH + 1) * 64 : 0)];
-  march_body<KH, TR, W>(v, f, dg, wt, r, ldr, rplane, hx, hy, hz, nx, ny, nz, xchunk, per, c, blockIdx.x,
+  __shared__ double lds[2 * TileGeo<KH, RW>::PLANE + (W ? (2 * KH + 1) * 64 : 0)];
+  march_body<KH, TR, W, RW>(v, f, dg, wt, r, ldr, rplane, hx, hy, hz, nx, ny, nz, xchunk, per, c, blockIdx.x,
                         blockIdx.y, blockIdx.z, lds, dot);
 }
 
 // Residuals of many solves (same k) in one launch: descriptor i owns blocks
 // [block0_i, block0_i + gx * gy * gz) of the grid; inactive solves are skipped.
-template <int KH, class TR>
+template <int KH, class TR, int RW>
 __global__ __launch_bounds__(RT) void residual_march_batch(const ResDesc* __restrict__ descs, int nd,
                                                              const int* __restrict__ active) {
-  __shared__ double lds[2 * TileGeo<KH>::PLANE];
+  __shared__ double lds[2 * TileGeo<KH, RW>::PLANE];
   const long i = blockIdx.x;
   int lo = 0, hi = nd;
   while (hi - lo > 1) {
@@ -363,7 +364,7 @@ __global__ __launch_bounds__(RT) void residual_march_batch(const ResDesc* __rest
   const int bx = (int)(rb % d.gx);
   const int by = (int)((rb / d.gx) % d.gy);
   const int bz = (int)(rb / ((long)d.gx * d.gy));
-  march_body<KH, TR, false>(d.v, d.f, d.d, nullptr, (TR*)d.r, d.ldr, d.rplane, d.hx, d.hy, d.hz, d.nx, d.ny, d.nz,
+  march_body<KH, TR, false, RW>(d.v, d.f, d.d, nullptr, (TR*)d.r, d.ldr, d.rplane, d.hx, d.hy, d.hz, d.nx, d.ny, d.nz,
                             d.xchunk, d.per, Coef{d.cf, d.cd, d.ch, 0.0}, bx, by, bz, lds);
 }
 
@@ -376,61 +377,86 @@ __global__ __launch_bounds__(RT) void residual_march_batch(const ResDesc* __rest
 // k = 4, 31^3 44 -> 9.2; (127, 163, 143) 55 -> 35.  With 1024 blocks as the line
 // k = 4, 255^3 takes 129 instead of 116 us, with 256 k = 8 takes 104.
 constexpr int MARCH_BLOCKS = 512;
+
+// Rows of y per wave.  Two rows share the y reads of a tile and a smaller halo, one
+// row leaves twice the blocks and half the registers, which wins while the march waits
+// for its loads rather than for bandwidth: on small arrays, and for k >= 6, whose
+// windows of 2 x 13 planes and more allow one block per CU.  FP64 residual with 2 / 1
+// rows: k = 4 (127, 163, 143) 34.7 / 26.9 us, k = 6 191^3 86.6 / 66.2, (257, 311, 227)
+// 211 / 184, k = 8 (191, 199, 119) 88.8 / 59.6; but k = 4 255^3 116 / 136, k = 5 249^3
+// 110 / 142, (59, 449, 449) 98 / 103.
+int march_rows(const int dims[3], int k) {
+  const long cols = (long)((dims[2] + TZ - 1) / TZ) * ((dims[1] + 15) / 16);
+  return k >= 6 || cols * ((dims[0] + 8 * k - 1) / (8 * k)) < 384 ? 1 : 2;
+}
+
 void march_grid(const int dims[3], int k, int* gx, int* gy, int* gz, int* xchunk) {
-  const long cols = (long)((dims[2] + RZ - 1) / RZ) * ((dims[1] + RY - 1) / RY);
+  const int ty = 8 * march_rows(dims, k);
+  *gx = (dims[2] + TZ - 1) / TZ;
+  *gy = (dims[1] + ty - 1) / ty;
+  const long cols = (long)*gx * *gy;
   int nchunks = (int)std::min<long>(dims[0], std::max<long>(1, (8192 + cols - 1) / cols));
   const int least = (int)std::min<long>(8L * k, std::max<long>(2, dims[0] * cols / MARCH_BLOCKS));
   *xchunk = std::max((dims[0] + nchunks - 1) / nchunks, std::min(dims[0], least));
-  *gx = (dims[2] + RZ - 1) / RZ;
-  *gy = (dims[1] + RY - 1) / RY;
   *gz = (dims[0] + *xchunk - 1) / *xchunk;
 }
 
-template <int KH, class TR>
-void launch_march(const ResidualArgs& ra, TR* r, const double* const hb[3], const int dims[3], Coef c,
-                  hipStream_t stream) {
+template <int KH, class TR, int RW>
+void launch_march_rows(const ResidualArgs& ra, TR* r, const double* const hb[3], const int dims[3], Coef c,
+                       hipStream_t stream) {
   int gx, gy, gz, xchunk;
   march_grid(dims, KH, &gx, &gy, &gz, &xchunk);
+  auto run = [&](auto kernel, const double* wt, const DotOut& dot) {
+    kernel<<<dim3(gx, gy, gz), dim3(RT), 0, stream>>>(ra.v, ra.f, ra.d, wt, r, ra.ldr, ra.rplane, hb[0], hb[1], hb[2],
+                                                      dims[0], dims[1], dims[2], xchunk, ra.periodic, c, dot);
+  };
   // the per-node weight (an FP64 operator application of the variable-coefficient
   // solver) has its own instantiation, so that the others keep their registers
   if constexpr (std::is_same<TR, double>::value) {
     if (ra.wt) {
       DotOut dot;
       if (ra.dot_partial) dot = DotOut{ra.dot_mass[0], ra.dot_mass[1], ra.dot_mass[2], ra.dot_partial};
-      if constexpr (KH == 4 || KH == 5)
-        residual_march_kernel_w4<KH, TR, true><<<dim3(gx, gy, gz), dim3(RT), 0, stream>>>(
-            ra.v, ra.f, ra.d, ra.wt, r, ra.ldr, ra.rplane, hb[0], hb[1], hb[2], dims[0], dims[1], dims[2], xchunk,
-            ra.periodic, c, dot);
+      if constexpr (RW == 2 && (KH == 4 || KH == 5))
+        run(residual_march_kernel_w4<KH, TR, true, RW>, ra.wt, dot);
       else
-        residual_march_kernel<KH, TR, true><<<dim3(gx, gy, gz), dim3(RT), 0, stream>>>(
-            ra.v, ra.f, ra.d, ra.wt, r, ra.ldr, ra.rplane, hb[0], hb[1], hb[2], dims[0], dims[1], dims[2], xchunk,
-            ra.periodic, c, dot);
+        run(residual_march_kernel<KH, TR, true, RW>, ra.wt, dot);
       return;
     }
   }
-  if constexpr (KH == 5) {
-    residual_march_kernel_w4<KH, TR, false><<<dim3(gx, gy, gz), dim3(RT), 0, stream>>>(
-        ra.v, ra.f, ra.d, nullptr, r, ra.ldr, ra.rplane, hb[0], hb[1], hb[2], dims[0], dims[1], dims[2], xchunk,
-        ra.periodic, c, DotOut());
-  } else {
-    residual_march_kernel<KH, TR, false><<<dim3(gx, gy, gz), dim3(RT), 0, stream>>>(
-        ra.v, ra.f, ra.d, nullptr, r, ra.ldr, ra.rplane, hb[0], hb[1], hb[2], dims[0], dims[1], dims[2], xchunk,
-        ra.periodic, c, DotOut());
-  }
+  if constexpr (RW == 2 && KH == 5)
+    run(residual_march_kernel_w4<KH, TR, false, RW>, nullptr, DotOut());
+  else
+    run(residual_march_kernel<KH, TR, false, RW>, nullptr, DotOut());
 }
 
-template <int KH>
-hipError_t batch_typed(int r_kind, const ResDesc* descs, int nd, long total_blocks, const int* active,
-                       hipStream_t s) {
+template <int KH, class TR>
+void launch_march(const ResidualArgs& ra, TR* r, const double* const hb[3], const int dims[3], Coef c,
+                  hipStream_t stream) {
+  if constexpr (KH < 6)
+    if (march_rows(dims, KH) == 2) return launch_march_rows<KH, TR, 2>(ra, r, hb, dims, c, stream);
+  launch_march_rows<KH, TR, 1>(ra, r, hb, dims, c, stream);
+}
+
+template <int KH, int RW>
+hipError_t batch_rows(int r_kind, const ResDesc* descs, int nd, long total_blocks, const int* active, hipStream_t s) {
   const dim3 grid((unsigned)total_blocks), block(RT);
   switch (r_kind) {
-    case 0: residual_march_batch<KH, double><<<grid, block, 0, s>>>(descs, nd, active); break;
-    case 1: residual_march_batch<KH, float><<<grid, block, 0, s>>>(descs, nd, active); break;
+    case 0: residual_march_batch<KH, double, RW><<<grid, block, 0, s>>>(descs, nd, active); break;
+    case 1: residual_march_batch<KH, float, RW><<<grid, block, 0, s>>>(descs, nd, active); break;
     case 2:
-    case 3: residual_march_batch<KH, unsigned short><<<grid, block, 0, s>>>(descs, nd, active); break;
+    case 3: residual_march_batch<KH, unsigned short, RW><<<grid, block, 0, s>>>(descs, nd, active); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <int KH>
+hipError_t batch_typed(int rows, int r_kind, const ResDesc* descs, int nd, long total_blocks, const int* active,
+                       hipStream_t s) {
+  if constexpr (KH < 6)
+    if (rows == 2) return batch_rows<KH, 2>(r_kind, descs, nd, total_blocks, active, s);
+  if (rows != 1) return hipErrorInvalidValue;
+  return batch_rows<KH, 1>(r_kind, descs, nd, total_blocks, active, s);
 }
 
 template <class TR>
@@ -466,7 +492,7 @@ hipError_t launch_residual(const ResidualArgs& ra, const double* const hb[3], in
   if (ra.wt && ra.r_kind != 0) return hipErrorInvalidValue;  // weights: FP64 output only
   if (ra.dot_partial && (!ra.wt || k > 8)) return hipErrorInvalidValue;  // fused dot: weighted march only
   // in-plane offsets are 32-bit; the grid's y and z extents are limited to 65535
-  if ((dims[1] + RY - 1) / RY > 65535 || dims[0] > 65535 || plane > 0x7fffffffL) return hipErrorInvalidValue;
+  if ((dims[1] + 7) / 8 > 65535 || dims[0] > 65535 || plane > 0x7fffffffL) return hipErrorInvalidValue;
   switch (ra.r_kind) {
     case 0: return launch_typed<double>(ra, (double*)ra.r, hb, k, dims, stream);
     case 1: return launch_typed<float>(ra, (float*)ra.r, hb, k, dims, stream);
@@ -509,6 +535,7 @@ bool residual_desc(const ResidualArgs& ra, const double* const hb[3], int k, con
   d->ny = dims[1];
   d->nz = dims[2];
   march_grid(dims, k, &d->gx, &d->gy, &d->gz, &d->xchunk);
+  d->rows = march_rows(dims, k);
   d->cf = ra.cf;
   d->cd = ra.cd;
   d->ch = ra.ch;
@@ -516,19 +543,19 @@ bool residual_desc(const ResidualArgs& ra, const double* const hb[3], int k, con
   return true;
 }
 
-hipError_t launch_residual_batch(int k, int r_kind, const ResDesc* descs, int nd, long total_blocks,
+hipError_t launch_residual_batch(int k, int rows, int r_kind, const ResDesc* descs, int nd, long total_blocks,
                                  const int* active, hipStream_t stream) {
   if (nd <= 0 || total_blocks <= 0) return hipSuccess;
   if (total_blocks > 0x7fffffffL) return hipErrorInvalidValue;
   switch (k) {
-    case 1: return batch_typed<1>(r_kind, descs, nd, total_blocks, active, stream);
-    case 2: return batch_typed<2>(r_kind, descs, nd, total_blocks, active, stream);
-    case 3: return batch_typed<3>(r_kind, descs, nd, total_blocks, active, stream);
-    case 4: return batch_typed<4>(r_kind, descs, nd, total_blocks, active, stream);
-    case 5: return batch_typed<5>(r_kind, descs, nd, total_blocks, active, stream);
-    case 6: return batch_typed<6>(r_kind, descs, nd, total_blocks, active, stream);
-    case 7: return batch_typed<7>(r_kind, descs, nd, total_blocks, active, stream);
-    case 8: return batch_typed<8>(r_kind, descs, nd, total_blocks, active, stream);
+    case 1: return batch_typed<1>(rows, r_kind, descs, nd, total_blocks, active, stream);
+    case 2: return batch_typed<2>(rows, r_kind, descs, nd, total_blocks, active, stream);
+    case 3: return batch_typed<3>(rows, r_kind, descs, nd, total_blocks, active, stream);
+    case 4: return batch_typed<4>(rows, r_kind, descs, nd, total_blocks, active, stream);
+    case 5: return batch_typed<5>(rows, r_kind, descs, nd, total_blocks, active, stream);
+    case 6: return batch_typed<6>(rows, r_kind, descs, nd, total_blocks, active, stream);
+    case 7: return batch_typed<7>(rows, r_kind, descs, nd, total_blocks, active, stream);
+    case 8: return batch_typed<8>(rows, r_kind, descs, nd, total_blocks, active, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -21,3 +21,9 @@ def test_residual(k, ne, bc):
     r = plan.residual(torch.from_numpy(u).cuda(), torch.from_numpy(f).cuda()).cpu().numpy()
     hnorm = sum(np.max(np.sum(np.abs(prob.h_dense(a)), axis=1)) for a in range(3)) + alpha
     assert np.max(np.abs(r - O.residual(prob, u, f))) <= 1e-14 * hnorm
+
+
+@pytest.mark.parametrize("k,ne,bc", [(3, (70, 60, 50), "neumann"), (6, (9, 30, 26), "periodic"), (8, (4, 3, 17), "neumann")])
+def test_residual_rows(k, ne, bc):
+    """Two rows of y per wave (large grids, k < 6) and one, ragged in y and z."""
+    test_residual(k, ne, bc)
