@@ -314,14 +314,16 @@ sem_status sem_batch_tile_rows(const sem_batch *b, int rows[6]);
  * arrays of count device pointers; u[i] must not alias f[i]).
  *  SEM_F32: the refinement of sem_solve_refined for every problem at once; each
  *           of the six mode products of an iteration is one persistent launch per
- *           tile shape over all still-unconverged problems, each residual one
- *           launch per k.  One synchronisation per iteration (norm read-back).
+ *           tile shape over all still-unconverged problems of less than 10^6
+ *           unknowns, each residual one launch per k and block shape; larger
+ *           problems run the products of sem_solve_refined, one launch each, on
+ *           three side streams that wait on and are joined back into the batch
+ *           stream, concurrently with the persistent launches.  One
+ *           synchronisation per iteration (norm read-back).
  *  SEM_BF16X3: as SEM_F32, except that every problem whose three dimensions are
  *           all >= 96 runs its iterations with the split-BF16 mode products of
- *           sem_solve_refined (one launch per pass, on three side streams that
- *           wait on and are joined back into the batch stream, concurrently with
- *           the persistent launches of the other problems); all problems refine
- *           in FP64 to the same tol.
+ *           sem_solve_refined on the side streams; all problems refine in FP64 to
+ *           the same tol.
  *  SEM_F64: one FP64 sem_solve per problem on the batch stream.
  * Every call (re)lays out each plan's low-precision workspace for the chosen
  * precision, so plans may be used by other calls between batch solves; the call

@@ -9,16 +9,19 @@
 // that meet the tolerance drop out through a per-solve active flag, so later
 // iterations only work on the rest.
 //
-// Split-BF16 batches (SEM_BF16X3): a solve whose every dimension reaches
-// SPLIT_MIN_DIM runs the split-BF16 passes of the single solves (right-hand-side
-// conversion, six DMA mode products, residual written as split BF16), one launch
-// per pass, on one of NSIDE side streams; the side streams run concurrently with
-// each other and with the persistent FP32 launches of the other solves on the
-// batch stream, so a small pass need not fill the chip by itself.  These passes
-// are 1.3-2.3x faster than the FP32 ones from n = 191 to 511 when run alone;
-// with the concurrency the batch time is flat for thresholds of 48..96 (245-249
-// ms for the 256-problem workload) and grows above (270 ms at 160, 343 at 256).
-// Both paths refine in FP64 to the same tolerance.
+// Solo solves: a solve of at least SOLO_MIN_N unknowns runs the products of the single
+// solves instead (FP32: the reflection-split strips, half the flops of the persistent
+// launches' dense products; in SEM_BF16X3 batches, with every dimension at least
+// SPLIT_MIN_DIM, the split-BF16 passes), one launch per product, on one of NSIDE side
+// streams; the side streams run concurrently with each other and with the persistent
+// launches of the other solves on the batch stream, so a small product need not fill
+// the chip by itself.  All solves refine in FP64 to the same tolerance.
+// Batches of 16 and 64 uneven problems (8..64 elements per axis) and of 6 (12..40), FP32
+// / BF16X3 in ms, by SOLO_MIN_N: none 17.9 / 9.1, 67.9 / 37.3, 2.97 / 1.72; 3e6 10.2 /
+// 9.0, 37.0 / 35.7, 1.69 / 1.70; 1e6 9.7 / 9.0, 36.3 / 35.5, 1.70 / 1.72; 3e5 9.9 / 9.3,
+// 36.5 / 35.6, 1.45 / 1.59, but 24 problems of 5..12 elements 1.01 -> 1.27.  With 1, 2, 4 or
+// 6 side streams 64 problems take 42.4, 37.6, 38.7, 36.8; SPLIT_MIN_DIM 48, 64 or 128
+// changes the BF16X3 times by -2 .. +8%.
 //
 // Tile shape: the FP32 kernel has 128 x 128, 96 x 128, 64 x 128 and 32 x 128 block tiles
 // (factor rows x tensor rows).  Short contraction lengths waste most of a
@@ -43,7 +46,8 @@ namespace {
 
 constexpr int NBUCKET = 6;
 constexpr int SPLIT_MIN_DIM = 96;
-// side streams of the split-BF16 solves (with the batch stream: the four hardware
+constexpr size_t SOLO_MIN_N = 1000000;
+// side streams of the solo solves (with the batch stream: the four hardware
 // queues a process gets by default)
 constexpr int NSIDE = 3;
 constexpr int TUNE_REPS = 5;
@@ -107,9 +111,9 @@ struct sem_batch {
   std::vector<ResDesc> h_rdesc;
   std::vector<Group> groups;
   std::vector<Group> rgroups;  // residual groups: var = k, tile_rows = rows of y per wave
-  hipStream_t side[NSIDE] = {nullptr, nullptr, nullptr};
+  hipStream_t side[NSIDE] = {};
   hipEvent_t ev_start = nullptr;
-  hipEvent_t ev_side[NSIDE] = {nullptr, nullptr, nullptr};
+  hipEvent_t ev_side[NSIDE] = {};
 };
 
 namespace semfd {
@@ -339,7 +343,8 @@ sem_status autotune(sem_batch* b) {
 // Low-precision factors of entry i's plan and the entry's workspace laid out for
 // prec: the plan's own workspace, or for a repeated plan the entry's own one.
 // Split-BF16 entries run the plan's own passes, whose launch shapes are tuned per
-// plan; the FP32 entries run the batch's grouped launches (tuned by autotune).
+// plan; the FP32 entries run strips, or the batch's grouped launches (tuned by
+// autotune).
 sem_status prepare_entry(sem_batch* b, int i, sem_prec prec) {
   sem_plan* p = b->plans[i];
   if (!b->repeat[i]) return lp_prepare(p, prec, &b->lw[i], prec != SEM_F32);
@@ -361,11 +366,11 @@ sem_status prepare_entry(sem_batch* b, int i, sem_prec prec) {
   return lp_layout(p, prec, b->own_ws[i], &b->lw[i]);
 }
 
-// One refinement iteration of solve i in split BF16 on `stream`: the FP64
-// residual written as split BF16 (from the second iteration on), then the FD
-// application that stores (first iteration) or accumulates the update into u and
+// One refinement iteration of solve i by itself on `stream`, in the precision of its
+// workspace: the FP64 residual in that format (from the second iteration on), then
+// the FD application that stores (first iteration) or accumulates the update into u and
 // leaves max|delta|, max|u| in the solve's norm slots.
-hipError_t split_iteration(sem_batch* b, int i, int it, const double* f, double* u, hipStream_t stream) {
+hipError_t solo_iteration(sem_batch* b, int i, int it, const double* f, double* u, hipStream_t stream) {
   sem_plan* p = b->plans[i];
   const LpWork& w = b->lw[i];
   hipStream_t keep = p->stream;
@@ -522,29 +527,30 @@ sem_status sem_batch_solve(sem_batch* b, sem_prec prec, double tol, int max_iter
   if (prec != SEM_F32 && prec != SEM_BF16X3)
     return set_error(SEM_EINVAL, "sem_batch_solve: batched solves run in SEM_F32, SEM_BF16X3 or SEM_F64");
   const int n = b->count;
-  // which solves run in split BF16; every solve's workspace is (re)laid out for
+  // which solves run by themselves; every solve's workspace is (re)laid out for
   // this call, since a plan's workspace may have moved since the last one
-  std::vector<char> split(n, 0);
+  std::vector<char> solo(n, 0);
   hipError_t e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) return hip_fail(e, "sem_batch_solve: stream");
   for (int i = 0; i < n; ++i) {
     const int* d = b->plans[i]->dims;
-    split[i] = prec == SEM_BF16X3 && std::min({d[0], d[1], d[2]}) >= SPLIT_MIN_DIM;
-    sem_status st = prepare_entry(b, i, split[i] ? SEM_BF16X3 : SEM_F32);
+    const bool split = prec == SEM_BF16X3 && std::min({d[0], d[1], d[2]}) >= SPLIT_MIN_DIM;
+    solo[i] = split || (b->plans[i]->N >= SOLO_MIN_N && f32_strips(b->plans[i]));
+    sem_status st = prepare_entry(b, i, split ? SEM_BF16X3 : SEM_F32);
     if (st != SEM_OK) return st;
   }
-  sem_status st = build_descs(b, f, u, split);
+  sem_status st = build_descs(b, f, u, solo);
   if (st != SEM_OK) return st;
-  // split solves: largest first onto the least-loaded side stream (cost ~ N (nx + ny + nz))
+  // solo solves: largest first onto the least-loaded side stream (cost ~ N (nx + ny + nz))
   std::vector<int> order, lane(n, 0);
   for (int i = 0; i < n; ++i)
-    if (split[i]) order.push_back(i);
+    if (solo[i]) order.push_back(i);
   auto cost = [&](int i) {
     const int* d = b->plans[i]->dims;
     return (double)d[0] * d[1] * d[2] * (d[0] + d[1] + d[2]);
   };
   std::sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
-  double load[NSIDE] = {0.0, 0.0, 0.0};
+  double load[NSIDE] = {};
   for (int i : order) {
     int s = 0;
     for (int t = 1; t < NSIDE; ++t)
@@ -562,13 +568,13 @@ sem_status sem_batch_solve(sem_batch* b, sem_prec prec, double tol, int max_iter
   sem_status result = SEM_OK;
   for (int it = 0; it < max_iter; ++it) {
     // the persistent launches see only the unconverged solves that they run
-    for (int i = 0; i < n; ++i) dev_active[i] = active[i] && !split[i];
+    for (int i = 0; i < n; ++i) dev_active[i] = active[i] && !solo[i];
     if ((e = hipMemcpyAsync(b->d_active, dev_active.data(), n * sizeof(int), hipMemcpyHostToDevice, b->stream)) !=
         hipSuccess)
       return hip_fail(e, "sem_batch_solve: active flags");
     batch_norms_zero<<<n, NORM_WORDS, 0, b->stream>>>(b->d_norms);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "sem_batch_solve: norm reset");
-    // split solves on the side streams, after the norm reset and concurrently with
+    // solo solves on the side streams, after the norm reset and concurrently with
     // the persistent launches below
     if (!order.empty()) {
       if ((e = hipEventRecord(b->ev_start, b->stream)) != hipSuccess) return hip_fail(e, "sem_batch_solve: event");
@@ -576,9 +582,9 @@ sem_status sem_batch_solve(sem_batch* b, sem_prec prec, double tol, int max_iter
         if ((e = hipStreamWaitEvent(b->side[s], b->ev_start, 0)) != hipSuccess)
           return hip_fail(e, "sem_batch_solve: event");
       for (int i : order)
-        if (active[i] && (e = split_iteration(b, i, it, f[i], u[i], b->side[lane[i]])) != hipSuccess) {
+        if (active[i] && (e = solo_iteration(b, i, it, f[i], u[i], b->side[lane[i]])) != hipSuccess) {
           drain();
-          return hip_fail(e, "sem_batch_solve: split-BF16 solve");
+          return hip_fail(e, "sem_batch_solve: solo solve");
         }
       for (int s = 0; s < NSIDE && e == hipSuccess; ++s) e = hipEventRecord(b->ev_side[s], b->side[s]);
       if (e != hipSuccess) {

@@ -100,6 +100,8 @@ sem_status lp_factors(sem_plan* p, sem_prec prec);
 sem_status lp_layout(sem_plan* p, sem_prec prec, void* ws, LpWork* w);
 hipError_t lp_fd(sem_plan* p, const LpWork& w, const Spectral& sp, const double* f64_src, double* u, int first,
                  unsigned long long* norms);
+// Whether the FP32 products of a plan run on strips (every axis up to 1024 nodes).
+bool f32_strips(const sem_plan* p);
 // FP64 FD application u = S_3 [g(L) (F_3 f)] on the reflection-split transforms
 // (tmp: N doubles; u may alias f).
 hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, double* tmp);

@@ -403,8 +403,7 @@ static void strip_factors(const T* g, int nrep, const void** fs, const void** fa
   *ba = g + 3 * block;
 }
 
-// Whether the FP32 products of a plan run on strips (every axis up to 1024 nodes).
-static bool f32_strips(const sem_plan* p) {
+bool f32_strips(const sem_plan* p) {
   for (int a = 0; a < 3; ++a)
     if (!strip_axis_ok(strip_axis(p, a), sizeof(float))) return false;
   return (long)p->dims[1] * p->dims[2] <= STRIP_MAX_Q;
