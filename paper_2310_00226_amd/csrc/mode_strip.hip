@@ -649,10 +649,14 @@ inline int strip_cols(long P, long Q, size_t line_bytes) {
 
 }  // namespace stripk
 
-// Waves of a strip block take one tile of 16 modes each (FP32: one or two), 16 waves
-// at most.
+// Waves of a strip block take one tile of 16 modes each, two past nrep = 256, 16 waves
+// at most: axes of up to 1024 nodes (1023 periodic), whose 16 FP64 lines fill 128 KB of
+// LDS.  FP64 solves with tiles / strips: 539^3 16.2 / 13.4 ms, 639^3 25.7 / 23.1, 799^3
+// 63.6 / 49.6, 999^3 119.9 / 99.6 (59.9 TFLOP/s of the halved products, 0.82 of what the
+// library's FP64 product reaches); FP32 application 999^3 104 / 61 ms.
 bool strip_axis_ok(const StripAxis& a, int elem) {
-  return a.nrep <= 16 * stripk::MAX_WAVES * (elem == 4 ? 2 : 1) && (size_t)stripk::pitch_rows(stripk::strip_len(a), elem) * elem * 16 <= stripk::LDS_MAX;
+  using namespace stripk;
+  return a.nrep <= 2 * 16 * MAX_WAVES && (size_t)pitch_rows(strip_len(a), elem) * elem * 16 <= LDS_MAX;
 }
 
 bool strip_plane_ok(const StripAxis& ay, const StripAxis& az, int elem) {
@@ -667,17 +671,19 @@ static hipError_t col_launch(StripArgs g, hipStream_t s) {
   const int waves = (g.ax.nrep + 16 * TT - 1) / (16 * TT);
   g.tiles = strip_tiles(g.ax.nrep);
   const size_t line = (size_t)strip_len(g.ax) * sizeof(T);
-  const int tc = strip_cols(g.P, g.Q, line);
+  // (FP64, two tiles a wave: 32 lines would spill at 16 waves)
+  constexpr bool WIDE = TT * sizeof(T) < 16;
+  const int tc = WIDE ? strip_cols(g.P, g.Q, line) : 1;
   g.ntiles = (g.Q + 16 * tc - 1) / (16 * tc) * g.P;
   const long blocks = (g.ntiles + 7) / 8 * 8;
-  if (tc == 1) return launch(col_kernel<T, TT, 1, OP, SPECTRAL>, g, blocks, waves, 16 * line, s);
-  return launch(col_kernel<T, TT, 2, OP, SPECTRAL>, g, blocks, waves, 32 * line, s);
+  if constexpr (WIDE)
+    if (tc == 2) return launch(col_kernel<T, TT, 2, OP, SPECTRAL>, g, blocks, waves, 32 * line, s);
+  return launch(col_kernel<T, TT, 1, OP, SPECTRAL>, g, blocks, waves, 16 * line, s);
 }
 
 template <class T, int OP, bool SPECTRAL = false>
 static hipError_t col_tiles(const StripArgs& g, hipStream_t s) {
-  if constexpr (sizeof(T) == 4)
-    if (g.ax.nrep > 16 * stripk::MAX_WAVES) return col_launch<T, 2, OP, SPECTRAL>(g, s);
+  if (g.ax.nrep > 16 * stripk::MAX_WAVES) return col_launch<T, 2, OP, SPECTRAL>(g, s);
   return col_launch<T, 1, OP, SPECTRAL>(g, s);
 }
 
@@ -699,17 +705,18 @@ static hipError_t row_launch(StripArgs g, hipStream_t s) {
   g.tiles = strip_tiles(g.ax.nrep);
   g.stride = pitch_rows(strip_len(g.ax), sizeof(T));
   const size_t line = (size_t)g.stride * sizeof(T);
-  const int tc = strip_cols(1, g.P, line);
+  constexpr bool WIDE = TT * sizeof(T) < 16;
+  const int tc = WIDE ? strip_cols(1, g.P, line) : 1;
   g.ntiles = (g.P + 16 * tc - 1) / (16 * tc);
   const long blocks = (g.ntiles + 7) / 8 * 8;
-  if (tc == 1) return launch(row_kernel<T, TI, TT, 1, OP>, g, blocks, waves, 16 * line, s);
-  return launch(row_kernel<T, TI, TT, 2, OP>, g, blocks, waves, 32 * line, s);
+  if constexpr (WIDE)
+    if (tc == 2) return launch(row_kernel<T, TI, TT, 2, OP>, g, blocks, waves, 32 * line, s);
+  return launch(row_kernel<T, TI, TT, 1, OP>, g, blocks, waves, 16 * line, s);
 }
 
 template <class T, class TI, int OP>
 static hipError_t row_tiles(const StripArgs& g, hipStream_t s) {
-  if constexpr (sizeof(T) == 4)
-    if (g.ax.nrep > 16 * stripk::MAX_WAVES) return row_launch<T, TI, 2, OP>(g, s);
+  if (g.ax.nrep > 16 * stripk::MAX_WAVES) return row_launch<T, TI, 2, OP>(g, s);
   return row_launch<T, TI, 1, OP>(g, s);
 }
 

@@ -640,8 +640,8 @@ sem_status lp_tune(sem_plan* p, const LpWork& w) {
 // antisymmetric]), so the multiplier reads the folded eigenvalues.
 // An axis that fits the strips of mode_strip.hip takes them: one launch per
 // product, forward, multiplier and backward of x in one launch, z and y in one
-// launch when the whole (y, z) plane fits.  Longer axes take the tiles of
-// mode_f64.hip, two launches per product.  There the antisymmetric blocks use only
+// launch when the whole (y, z) plane fits.  Axes of more than 1024 nodes take the tiles
+// of mode_f64.hip, two launches per product.  There the antisymmetric blocks use only
 // the nodd representatives that are not their own reflection (r = j + off, off = 1
 // on periodic axes, whose node 0 is fixed; the fixed node of an odd non-periodic
 // axis is the last representative), whose v- is not identically 0:

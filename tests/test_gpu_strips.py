@@ -50,16 +50,24 @@ def test_separate_axes_at_strip_edges(ne, bc):
 
 
 @pytest.mark.parametrize("long_axes", [(0,), (1,), (2,), (0, 1), (0, 2), (1, 2)])
-@pytest.mark.parametrize("n,bc", [(511, D), (512, C), (513, N)])
-def test_long_axes(long_axes, n, bc):
-    """The last length a strip takes (nrep = 256) and the first of the tiles, on every
-    set of axes: the two kinds of products hand over to each other."""
-    ne = [6, 3, 4]
+@pytest.mark.parametrize("ne,bc", [(128, D), (128, C), (128, N)])
+def test_two_tiles_a_wave(long_axes, ne, bc):
+    """nrep = 256 and 257, the last with one tile of modes a wave and the first with two."""
+    mesh = [6, 3, 4]
     for a in long_axes:
-        ne[a] = 128
-    prob_axis = {D: 4 * 128 - 1, N: 4 * 128 + 1, C: 4 * 128}[bc]
-    assert prob_axis == n
-    _check(4, tuple(ne), bc)
+        mesh[a] = ne
+    _check(4, tuple(mesh), bc)
+
+
+@pytest.mark.parametrize("long_axes", [(0,), (1,), (2,), (0, 1), (0, 2), (1, 2)])
+@pytest.mark.parametrize("bc", [D, N])
+def test_past_the_strips(long_axes, bc):
+    """The last length a strip takes (1023, nrep = 512) and the first of the tiles (1025)
+    on every set of axes: the two kinds of products hand over to each other."""
+    mesh = [2, 1, 2]
+    for a in long_axes:
+        mesh[a] = 256
+    _check(4, tuple(mesh), bc)
 
 
 def _check_f32(k, ne, bc):
