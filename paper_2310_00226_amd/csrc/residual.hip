@@ -314,32 +314,20 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
   }
 }
 
-template <int KH, class TR, bool W, int RW>
-__global__ __launch_bounds__(RT) void residual_march_kernel(const double* __restrict__ v,
-                                                                  const double* __restrict__ f,
-                                                                  const double* __restrict__ dg,
-                                                                  const double* __restrict__ wt, TR* __restrict__ r,
-                                                                  int ldr, long rplane,
-                                                                  const double* __restrict__ hx,
-                                                                  const double* __restrict__ hy,
-                                                                  const double* __restrict__ hz, int nx, int ny,
-                                                                  int nz, int xchunk, int per, Coef c,
-                                                                  DotOut dot) {
-  __shared__ double lds[2 * TileGeo<KH, RW>::PLANE + (W ? (2 * KH + 1) * 64 : 0)];
-  march_body<KH, TR, W, RW>(v, f, dg, wt, r, ldr, rplane, hx, hy, hz, nx, ny, nz, xchunk, per, c, blockIdx.x,
-                        blockIdx.y, blockIdx.z, lds, dot);
+// Waves per SIMD that a march is compiled for: 4 (at most 128 VGPRs, two blocks per CU)
+// where it would otherwise take a few registers more and hold one block per CU (k = 5
+// 130 instead of 127: 1000^3 6.8 instead of 6.1 ms).
+template <int KH, int RW>
+constexpr int march_waves() {
+  return (RW == 2 && KH >= 3) || KH == 8 ? 4 : 2;
 }
 
-// The same march with at most 128 VGPRs (4 waves per SIMD, two blocks per CU).
-// For k = 5 without the weight it fits without spilling (127 instead of 130
-// VGPRs) and runs 10% faster (6.1 vs 6.8 ms at 1000^3); the weighted k = 5
-// march would spill 44 bytes per lane and gain nothing, k = 4 fits either way.
 template <int KH, class TR, bool W, int RW>
-__global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(4, 8))) void residual_march_kernel_w4(
-    const double* __restrict__ v, const double* __restrict__ f, const double* __restrict__ dg,
-    const double* __restrict__ wt, TR* __restrict__ r, int ldr, long rplane, const double* __restrict__ hx,
-    const double* __restrict__ hy, const double* __restrict__ hz, int nx, int ny, int nz, int xchunk, int per,
-    Coef c, DotOut dot) {
+__global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(march_waves<KH, RW>(), 8))) void
+residual_march_kernel(const double* __restrict__ v, const double* __restrict__ f, const double* __restrict__ dg,
+                      const double* __restrict__ wt, TR* __restrict__ r, int ldr, long rplane,
+                      const double* __restrict__ hx, const double* __restrict__ hy, const double* __restrict__ hz,
+                      int nx, int ny, int nz, int xchunk, int per, Coef c, DotOut dot) {
   __shared__ double lds[2 * TileGeo<KH, RW>::PLANE + (W ? (2 * KH + 1) * 64 : 0)];
   march_body<KH, TR, W, RW>(v, f, dg, wt, r, ldr, rplane, hx, hy, hz, nx, ny, nz, xchunk, per, c, blockIdx.x,
                         blockIdx.y, blockIdx.z, lds, dot);
@@ -368,15 +356,17 @@ __global__ __launch_bounds__(RT) void residual_march_batch(const ResDesc* __rest
                             d.xchunk, d.per, Coef{d.cf, d.cd, d.ch, 0.0}, bx, by, bz, lds);
 }
 
-// x is split into chunks so that the grid fills the chip even for thin (y, z)
-// planes.  A chunk spans at least 8 k planes, since each chunk first loads the 2k
-// planes of its window, unless that leaves fewer than two blocks per CU: a plane
-// of the march is a serial step of about 1 us, so short chunks with the window
-// loads overlapped win there.  FP64 residual, 8 k planes against this rule: k = 5,
-// 119^3 (16 columns of blocks) 77.8 -> 23.6 us; k = 8, (191, 199, 119) 167 -> 89;
-// k = 4, 31^3 44 -> 9.2; (127, 163, 143) 55 -> 35.  With 1024 blocks as the line
-// k = 4, 255^3 takes 129 instead of 116 us, with 256 k = 8 takes 104.
-constexpr int MARCH_BLOCKS = 512;
+// x is split into chunks so that the grid fills the chip even for thin (y, z) planes.
+// The blocks run in rounds of MARCH_SLOTS (two per CU, see march_waves): the time follows
+// rounds x (planes of a chunk + 3), the 3 for the window loads and the start of a block,
+// and a few blocks more than a full round cost a whole one.  The chunk is the cheapest
+// with as many blocks as fit 1, 2, .. 32 rounds, the shortest of those within 3%, since
+// blocks of many rounds drift apart and overlap.  FP64 residual with the line of 512
+// blocks alone (batches keep it: there the blocks of other solves fill a round) / this
+// rule: k = 4 257^3 157 (680 blocks) -> 117 us (510), 199^3 66 -> 61; k = 5 119^3 23.1 ->
+// 18.3; k = 6 (257, 311, 227) 184 -> 171, 191^3 67 -> 61; k = 7 209^3 120 -> 101; k = 8
+// (191, 199, 119) 59 -> 52, 511^3 1083 -> 1069.
+constexpr int MARCH_SLOTS = 512;
 
 // Rows of y per wave.  Two rows share the y reads of a tile and a smaller halo, one
 // row leaves twice the blocks and half the registers, which wins while the march waits
@@ -390,14 +380,40 @@ int march_rows(const int dims[3], int k) {
   return k >= 6 || cols * ((dims[0] + 8 * k - 1) / (8 * k)) < 384 ? 1 : 2;
 }
 
-void march_grid(const int dims[3], int k, int* gx, int* gy, int* gz, int* xchunk) {
+void march_tiles(const int dims[3], int k, int* gx, int* gy) {
   const int ty = 8 * march_rows(dims, k);
   *gx = (dims[2] + TZ - 1) / TZ;
   *gy = (dims[1] + ty - 1) / ty;
+}
+
+void march_grid(const int dims[3], int k, int* gx, int* gy, int* gz, int* xchunk) {
+  march_tiles(dims, k, gx, gy);
   const long cols = (long)*gx * *gy;
-  int nchunks = (int)std::min<long>(dims[0], std::max<long>(1, (8192 + cols - 1) / cols));
-  const int least = (int)std::min<long>(8L * k, std::max<long>(2, dims[0] * cols / MARCH_BLOCKS));
-  *xchunk = std::max((dims[0] + nchunks - 1) / nchunks, std::min(dims[0], least));
+  long best = 0;
+  *xchunk = dims[0];
+  for (long m = 1; m <= 32; ++m) {
+    const long g = std::min<long>(MARCH_SLOTS * m / cols, std::max(1, dims[0] / 2));
+    if (g < 1) continue;
+    const int chunk = (int)((dims[0] + g - 1) / g);
+    const long rounds = (cols * ((dims[0] + chunk - 1) / chunk) + MARCH_SLOTS - 1) / MARCH_SLOTS;
+    const long cost = rounds * (chunk + 3);
+    if (best && cost * 32 > best * 33) continue;
+    best = best ? std::min(best, cost) : cost;
+    *xchunk = chunk;
+  }
+  *gz = (dims[0] + *xchunk - 1) / *xchunk;
+}
+
+// The chunks of one solve of a batch: at least 8 k planes, since each first loads the 2k
+// planes of its window, unless that leaves it fewer than two blocks per CU; a plane of the
+// march is a serial step of about 1 us, so short chunks win there (k = 5 119^3 77.8 ->
+// 23.6 us alone).  The rule of rounds above is no faster here (16 solves of 39^3..450^3,
+// split BF16 8.99 / 9.02 ms; FP32 9.60 / 9.60).
+void march_grid_batch(const int dims[3], int k, int* gx, int* gy, int* gz, int* xchunk) {
+  march_tiles(dims, k, gx, gy);
+  const long cols = (long)*gx * *gy;
+  const int least = (int)std::min<long>(8L * k, std::max<long>(2, dims[0] * cols / MARCH_SLOTS));
+  *xchunk = (int)std::min<long>(dims[0], std::max<long>((dims[0] * cols + 8191) / 8192, least));
   *gz = (dims[0] + *xchunk - 1) / *xchunk;
 }
 
@@ -416,17 +432,11 @@ void launch_march_rows(const ResidualArgs& ra, TR* r, const double* const hb[3],
     if (ra.wt) {
       DotOut dot;
       if (ra.dot_partial) dot = DotOut{ra.dot_mass[0], ra.dot_mass[1], ra.dot_mass[2], ra.dot_partial};
-      if constexpr (RW == 2 && (KH == 4 || KH == 5))
-        run(residual_march_kernel_w4<KH, TR, true, RW>, ra.wt, dot);
-      else
-        run(residual_march_kernel<KH, TR, true, RW>, ra.wt, dot);
+      run(residual_march_kernel<KH, TR, true, RW>, ra.wt, dot);
       return;
     }
   }
-  if constexpr (RW == 2 && KH == 5)
-    run(residual_march_kernel_w4<KH, TR, false, RW>, nullptr, DotOut());
-  else
-    run(residual_march_kernel<KH, TR, false, RW>, nullptr, DotOut());
+  run(residual_march_kernel<KH, TR, false, RW>, nullptr, DotOut());
 }
 
 template <int KH, class TR>
@@ -534,7 +544,7 @@ bool residual_desc(const ResidualArgs& ra, const double* const hb[3], int k, con
   d->nx = dims[0];
   d->ny = dims[1];
   d->nz = dims[2];
-  march_grid(dims, k, &d->gx, &d->gy, &d->gz, &d->xchunk);
+  march_grid_batch(dims, k, &d->gx, &d->gy, &d->gz, &d->xchunk);
   d->rows = march_rows(dims, k);
   d->cf = ra.cf;
   d->cd = ra.cd;

@@ -27,3 +27,9 @@ def test_residual(k, ne, bc):
 def test_residual_rows(k, ne, bc):
     """Two rows of y per wave (large grids, k < 6) and one, ragged in y and z."""
     test_residual(k, ne, bc)
+
+
+@pytest.mark.parametrize("k,ne,bc", [(4, (64, 64, 64), "neumann"), (7, (30, 30, 30), "dirichlet"), (5, (3, 90, 90), "periodic")])
+def test_residual_rounds(k, ne, bc):
+    """Chunks of one full round of blocks, of two, and more columns than a round has."""
+    test_residual(k, ne, bc)
