@@ -277,8 +277,8 @@ sem_status sem_pcg_workspace_bytes(const sem_plan *p, size_t *bytes);
  *        The preconditioner also uses the plan workspace.
  *  iters / relres / shift_used (may be NULL): iterations, final ||r||_M / ||f||_M
  *        and the shift the preconditioner used.
- * Synchronises with the plan stream once per inner product (three per iteration),
- * and once more for the default shift.
+ * Synchronises with the plan stream once per iteration, once at the start, and once
+ * more for the default shift.
  * SEM_EINVAL: null pointers, aliasing, a non-finite shift, a default shift that is
  * not > 0, tol < 0, max_iter < 1, small or misaligned workspace.  SEM_ENOCONV: tol
  * not met within max_iter, or a non-positive curvature (V too negative: A not

@@ -14,9 +14,15 @@
 // z = P^{-1} r (an FP64 FD solve, or a low-precision one); <r, z> (and <z, q>);
 // p = z + b p.  With a BF16 preconditioner (reflection-split passes) the update
 // also writes the new r folded along z in BF16, the input of the preconditioner's
-// first pass, and the preconditioner's unfold into z forms <r, z> and <z, q>.  The weighted inner products are two-stage block reductions
-// (fixed block count, partial sums added in a fixed order: deterministic); the
-// mass weight of node (i, j, l) is Mx_i My_j Mz_l from the three 1D masses.
+// first pass, and the preconditioner's unfold into z forms <r, z> and <z, q>.  The
+// weighted inner products are two-stage block reductions (fixed block count, partial
+// sums added in a fixed order: deterministic); the mass weight of node (i, j, l) is
+// Mx_i My_j Mz_l from the three 1D masses.
+//
+// The step lengths stay on the device: pcg_scalars adds up the partial sums and the
+// kernels that follow read a and b there, so that the host waits once per iteration, for
+// the residual norm.  With a copy to the host and a wait per inner product an iteration
+// had three gaps of about 15 us (k = 5 249^3, split BF16: 808 instead of 751 us).
 //
 // With a low-precision preconditioner the operator P^{-1} varies slightly from
 // one application to the next, so b uses the flexible (Polak-Ribiere) form
@@ -41,6 +47,16 @@ constexpr int DOT_BLOCKS = 4096, DOT_THREADS = 256, MAXDOT = 2;
 
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
+// Scalars of the iteration in device memory: <p, q>, <r, r>, <r, z> and the step b.
+enum { S_PQ, S_RR, S_RZ, S_B, S_COUNT };
+
+// An iterate that the update may use; the host makes the same test once it has the
+// values, so a breakdown leaves u as it was.
+__host__ __device__ inline bool step_ok(double pq, double rz) {
+  return pq > 0.0 && rz > 0.0 && pq <= DBL_MAX && rz <= DBL_MAX;
+}
+
+template <int THREADS = DOT_THREADS>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -48,7 +64,7 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   __syncthreads();
   double t = 0.0;
   if (threadIdx.x == 0)
-    for (int w = 0; w < DOT_THREADS / 64; ++w) t += sh[w];
+    for (int w = 0; w < THREADS / 64; ++w) t += sh[w];
   __syncthreads();
   return t;  // valid in thread 0
 }
@@ -85,15 +101,18 @@ __global__ __launch_bounds__(DOT_THREADS) void mdot_partial(const double* __rest
   }
 }
 
-// u += a p, r -= a q, and the partial sums of <r, r> (new r).
+// u += a p, r -= a q with a = <r, z> / <p, q>, and the partial sums of <r, r> (new r).
 __global__ __launch_bounds__(DOT_THREADS) void pcg_update(double* __restrict__ u, double* __restrict__ r,
                                                           const double* __restrict__ p,
-                                                          const double* __restrict__ q, double a,
+                                                          const double* __restrict__ q,
+                                                          const double* __restrict__ scal,
                                                           const double* __restrict__ mx,
                                                           const double* __restrict__ my,
                                                           const double* __restrict__ mz, int nx, int ny, int nz,
                                                           double* __restrict__ partial) {
   __shared__ double sh[DOT_THREADS / 64];
+  if (!step_ok(scal[S_PQ], scal[S_RZ])) return;  // the whole grid
+  const double a = scal[S_RZ] / scal[S_PQ];
   double s = 0.0;
   const long rows = (long)nx * ny;
   for (long row = blockIdx.x; row < rows; row += gridDim.x) {
@@ -122,7 +141,8 @@ __global__ __launch_bounds__(DOT_THREADS) void pcg_update(double* __restrict__ u
 template <int NS>
 __global__ __launch_bounds__(DOT_THREADS) void pcg_update_fold(double* __restrict__ u, double* __restrict__ r,
                                                                const double* __restrict__ p,
-                                                               const double* __restrict__ q, double a,
+                                                               const double* __restrict__ q,
+                                                          const double* __restrict__ scal,
                                                                const double* __restrict__ mx,
                                                                const double* __restrict__ my,
                                                                const double* __restrict__ mz, int nx, int ny, int nz,
@@ -130,6 +150,8 @@ __global__ __launch_bounds__(DOT_THREADS) void pcg_update_fold(double* __restric
                                                                unsigned short* __restrict__ o, long plane_o, int nrep,
                                                                int fpad, int per) {
   __shared__ double sh[DOT_THREADS / 64];
+  if (!step_ok(scal[S_PQ], scal[S_RZ])) return;  // the whole grid
+  const double a = scal[S_RZ] / scal[S_PQ];
   double s = 0.0;
   const long rows = (long)nx * ny;
   for (long row = blockIdx.x; row < rows; row += gridDim.x) {
@@ -170,15 +192,32 @@ __global__ __launch_bounds__(DOT_THREADS) void pcg_update_fold(double* __restric
   if (threadIdx.x == 0) partial[(size_t)blockIdx.x * MAXDOT] = t;
 }
 
-// Fixed-order sum of the block partials: out[d] = sum_b partial[b][d].
-__global__ __launch_bounds__(DOT_THREADS) void mdot_final(const double* __restrict__ partial, int nblocks, int ndot,
-                                                          double* __restrict__ out) {
-  __shared__ double sh[DOT_THREADS / 64];
-  for (int d = 0; d < ndot; ++d) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += DOT_THREADS) s += partial[(size_t)b * MAXDOT + d];
-    const double t = block_sum(s, sh);
-    if (threadIdx.x == 0) out[d] = t;
+// Fixed-order sums of the block partials, and what the iteration takes from them: one
+// block, so its time is the latency of its loads, a few per thread.
+//   SUM_PQ, SUM_RR, SUM_RZ: <p, q>, <r, r>, the first <r, z>;
+//   NEXT_RZ: the next <r, z>, b = <r, z> / <r, z>_old;
+//   NEXT_RZ_ZQ: the same with the flexible b = -a <z, q> / <r, z>_old.
+enum { SUM_PQ, SUM_RR, SUM_RZ, NEXT_RZ, NEXT_RZ_ZQ };
+constexpr int SUM_THREADS = 1024;
+__global__ __launch_bounds__(SUM_THREADS) void pcg_scalars(const double* __restrict__ partial, int nblocks, int op,
+                                                           double* __restrict__ scal) {
+  __shared__ double sh[SUM_THREADS / 64];
+  double s0 = 0.0, s1 = 0.0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nblocks; b += SUM_THREADS) {
+    s0 += partial[(size_t)b * MAXDOT];
+    if (op == NEXT_RZ_ZQ) s1 += partial[(size_t)b * MAXDOT + 1];
+  }
+  const double t = block_sum<SUM_THREADS>(s0, sh);
+  const double zq = op == NEXT_RZ_ZQ ? block_sum<SUM_THREADS>(s1, sh) : 0.0;
+  if (threadIdx.x != 0) return;
+  if (op == SUM_PQ) scal[S_PQ] = t;
+  else if (op == SUM_RR) scal[S_RR] = t;
+  else {
+    const double rz = scal[S_RZ];
+    if (op == NEXT_RZ) scal[S_B] = t / rz;
+    if (op == NEXT_RZ_ZQ) scal[S_B] = -(rz / scal[S_PQ]) * zq / rz;
+    scal[S_RZ] = t;
   }
 }
 
@@ -220,14 +259,15 @@ __global__ __launch_bounds__(DOT_THREADS) void default_shift(const double* __res
 }
 
 // p = z + b p
-__global__ __launch_bounds__(256) void pcg_direction(double* __restrict__ p, const double* __restrict__ z, double b,
-                                                     size_t n) {
+__global__ __launch_bounds__(256) void pcg_direction(double* __restrict__ p, const double* __restrict__ z,
+                                                     const double* __restrict__ scal, size_t n) {
+  const double b = scal[S_B];
   for (size_t g = (size_t)blockIdx.x * blockDim.x + threadIdx.x; g < n; g += (size_t)gridDim.x * blockDim.x)
     p[g] = z[g] + b * p[g];
 }
 
 struct PcgWork {
-  double *r, *z, *p, *q, *partial, *out;
+  double *r, *z, *p, *q, *partial, *scal;
 };
 
 // block partials: the dot kernels' DOT_BLOCKS, or the operator march's blocks
@@ -244,21 +284,28 @@ int dot_blocks(const sem_plan* p) {
   return (int)(rows < DOT_BLOCKS ? rows : DOT_BLOCKS);
 }
 
-// <a0, b0> (and <a1, b1>) into host h[0..ndot)
-hipError_t mdot(sem_plan* p, const PcgWork& w, int ndot, const double* a0, const double* b0, const double* a1,
-                const double* b1, double* h) {
+hipError_t scalars(sem_plan* p, const PcgWork& w, long nblocks, int op) {
+  pcg_scalars<<<1, SUM_THREADS, 0, p->stream>>>(w.partial, (int)nblocks, op, w.scal);
+  return hipGetLastError();
+}
+
+// <a0, b0> (and <a1, b1>) as op takes them
+hipError_t mdot(sem_plan* p, const PcgWork& w, int op, const double* a0, const double* b0, const double* a1 = nullptr,
+                const double* b1 = nullptr) {
   const int nb = dot_blocks(p);
-  if (ndot == 1)
+  if (op != NEXT_RZ_ZQ)
     mdot_partial<1><<<nb, DOT_THREADS, 0, p->stream>>>(a0, b0, a0, b0, p->d_mass[0], p->d_mass[1], p->d_mass[2],
                                                        p->dims[0], p->dims[1], p->dims[2], w.partial);
   else
     mdot_partial<2><<<nb, DOT_THREADS, 0, p->stream>>>(a0, b0, a1, b1, p->d_mass[0], p->d_mass[1], p->d_mass[2],
                                                        p->dims[0], p->dims[1], p->dims[2], w.partial);
-  mdot_final<<<1, DOT_THREADS, 0, p->stream>>>(w.partial, nb, ndot, w.out);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(h, w.out, ndot * sizeof(double), hipMemcpyDeviceToHost, p->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
-  return e;
+  return scalars(p, w, nb, op);
+}
+
+// the first count scalars into host h
+hipError_t fetch(sem_plan* p, const PcgWork& w, double* h, int count) {
+  hipError_t e = hipMemcpyAsync(h, w.scal, count * sizeof(double), hipMemcpyDeviceToHost, p->stream);
+  return e == hipSuccess ? hipStreamSynchronize(p->stream) : e;
 }
 
 }  // namespace
@@ -296,15 +343,13 @@ sem_status sem_pcg_solve(sem_plan* p, const double* v, double shift, sem_prec pr
             (double*)(wb + 4 * vb), (double*)(wb + 4 * vb + align256(partial_slots(p) * MAXDOT * sizeof(double)))};
 
   hipError_t e;
-  double h[2];
+  double h[S_COUNT];
   if (!(shift > 0.0)) {
     // default: the paper's alpha + beta / 2 with beta = max(V)
     const int nb0 = dot_blocks(p);
     vmax_partial<<<nb0, DOT_THREADS, 0, p->stream>>>(v, n, w.partial);
-    default_shift<<<1, DOT_THREADS, 0, p->stream>>>(w.partial, nb0, p->alpha, w.out);
-    if ((e = hipGetLastError()) != hipSuccess ||
-        (e = hipMemcpyAsync(h, w.out, sizeof(double), hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
-        (e = hipStreamSynchronize(p->stream)) != hipSuccess)
+    default_shift<<<1, DOT_THREADS, 0, p->stream>>>(w.partial, nb0, p->alpha, w.scal);
+    if ((e = hipGetLastError()) != hipSuccess || (e = fetch(p, w, h, 1)) != hipSuccess)
       return hip_fail(e, "sem_pcg_solve: default shift");
     shift = h[0];
     if (!std::isfinite(shift)) return set_error(SEM_ENONFINITE, "sem_pcg_solve: non-finite potential");
@@ -372,83 +417,58 @@ sem_status sem_pcg_solve(sem_plan* p, const double* v, double shift, sem_prec pr
   // u = 0, r = f
   if ((e = hipMemsetAsync(u, 0, n * sizeof(double), p->stream)) != hipSuccess ||
       (e = hipMemcpyAsync(w.r, f, n * sizeof(double), hipMemcpyDeviceToDevice, p->stream)) != hipSuccess ||
-      (e = mdot(p, w, 1, f, f, nullptr, nullptr, h)) != hipSuccess)
+      (e = mdot(p, w, SUM_RR, f, f)) != hipSuccess || (e = fetch(p, w, h, S_RR + 1)) != hipSuccess)
     return hip_fail(e, "sem_pcg_solve: start");
-  const double fn2 = h[0];
+  const double fn2 = h[S_RR];
   if (!std::isfinite(fn2)) return set_error(SEM_ENONFINITE, "sem_pcg_solve: non-finite right-hand side");
   if (fn2 == 0.0) {
     if (relres) *relres = 0.0;
     return SEM_OK;
   }
-  if ((e = precondition()) != hipSuccess || (e = mdot(p, w, 1, w.r, w.z, nullptr, nullptr, h)) != hipSuccess ||
+  if ((e = precondition()) != hipSuccess || (e = mdot(p, w, SUM_RZ, w.r, w.z)) != hipSuccess ||
       (e = hipMemcpyAsync(w.p, w.z, n * sizeof(double), hipMemcpyDeviceToDevice, p->stream)) != hipSuccess)
     return hip_fail(e, "sem_pcg_solve: first preconditioner application");
-  double rz = h[0];
   double rel = 1.0;
   for (int it = 1; it <= max_iter; ++it) {
     if ((e = launch_residual(ra, hb, p->k, p->dims, p->stream)) != hipSuccess)
       return hip_fail(e, "sem_pcg_solve: operator");
-    if (fused_blocks > 0) {
-      mdot_final<<<1, DOT_THREADS, 0, p->stream>>>(w.partial, (int)fused_blocks, 1, w.out);
-      if ((e = hipGetLastError()) != hipSuccess ||
-          (e = hipMemcpyAsync(h, w.out, sizeof(double), hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
-          (e = hipStreamSynchronize(p->stream)) != hipSuccess)
-        return hip_fail(e, "sem_pcg_solve: <p, q>");
-    } else if ((e = mdot(p, w, 1, w.p, w.q, nullptr, nullptr, h)) != hipSuccess) {
-      return hip_fail(e, "sem_pcg_solve: <p, q>");
-    }
-    const double pq = h[0];
-    if (!std::isfinite(pq) || !std::isfinite(rz)) return set_error(SEM_ENONFINITE, "sem_pcg_solve: non-finite iterate");
-    if (!(pq > 0.0) || !(rz > 0.0))
-      return set_error(SEM_ENOCONV, "sem_pcg_solve: operator or preconditioner not positive definite");
-    const double a = rz / pq;
+    e = fused_blocks > 0 ? scalars(p, w, fused_blocks, SUM_PQ) : mdot(p, w, SUM_PQ, w.p, w.q);
+    if (e != hipSuccess) return hip_fail(e, "sem_pcg_solve: <p, q>");
     if (fold_update) {
       // the update also writes the preconditioner's folded BF16 input
       if (prec == SEM_BF16X3)
         pcg_update_fold<2><<<nb, DOT_THREADS, 0, p->stream>>>(
-            u, w.r, w.p, w.q, a, p->d_mass[0], p->d_mass[1], p->d_mass[2], p->dims[0], p->dims[1], p->dims[2],
+            u, w.r, w.p, w.q, w.scal, p->d_mass[0], p->d_mass[1], p->d_mass[2], p->dims[0], p->dims[1], p->dims[2],
             w.partial, (unsigned short*)lw.t1, lw.tplane, fz.nrep, fz.pad, fz.per);
       else
         pcg_update_fold<1><<<nb, DOT_THREADS, 0, p->stream>>>(
-            u, w.r, w.p, w.q, a, p->d_mass[0], p->d_mass[1], p->d_mass[2], p->dims[0], p->dims[1], p->dims[2],
+            u, w.r, w.p, w.q, w.scal, p->d_mass[0], p->d_mass[1], p->d_mass[2], p->dims[0], p->dims[1], p->dims[2],
             w.partial, (unsigned short*)lw.t1, lw.tplane, fz.nrep, fz.pad, fz.per);
       lw.input_in_t1 = true;
       lw.unfold_dot = &ud;
     } else {
-      pcg_update<<<nb, DOT_THREADS, 0, p->stream>>>(u, w.r, w.p, w.q, a, p->d_mass[0], p->d_mass[1], p->d_mass[2],
-                                                     p->dims[0], p->dims[1], p->dims[2], w.partial);
+      pcg_update<<<nb, DOT_THREADS, 0, p->stream>>>(u, w.r, w.p, w.q, w.scal, p->d_mass[0], p->d_mass[1],
+                                                     p->d_mass[2], p->dims[0], p->dims[1], p->dims[2], w.partial);
     }
-    mdot_final<<<1, DOT_THREADS, 0, p->stream>>>(w.partial, nb, 1, w.out);
-    if ((e = hipGetLastError()) != hipSuccess ||
-        (e = hipMemcpyAsync(h, w.out, sizeof(double), hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
-        (e = hipStreamSynchronize(p->stream)) != hipSuccess)
+    if ((e = hipGetLastError()) != hipSuccess || (e = scalars(p, w, nb, SUM_RR)) != hipSuccess ||
+        (e = fetch(p, w, h, S_RZ + 1)) != hipSuccess)
       return hip_fail(e, "sem_pcg_solve: update");
-    rel = std::sqrt(h[0] / fn2);
+    if (!std::isfinite(h[S_PQ]) || !std::isfinite(h[S_RZ]))
+      return set_error(SEM_ENONFINITE, "sem_pcg_solve: non-finite iterate");
+    if (!step_ok(h[S_PQ], h[S_RZ]))
+      return set_error(SEM_ENOCONV, "sem_pcg_solve: operator or preconditioner not positive definite");
+    rel = std::sqrt(h[S_RR] / fn2);
     if (iters) *iters = it;
     if (relres) *relres = rel;
     if (!std::isfinite(rel)) return set_error(SEM_ENONFINITE, "sem_pcg_solve: non-finite residual");
     if (rel <= tol) return SEM_OK;
     if (it == max_iter) break;
     if ((e = precondition()) != hipSuccess) return hip_fail(e, "sem_pcg_solve: preconditioner");
-    double b;
-    if (prec == SEM_F64) {
-      if ((e = mdot(p, w, 1, w.r, w.z, nullptr, nullptr, h)) != hipSuccess) return hip_fail(e, "sem_pcg_solve: dot");
-      b = h[0] / rz;
-      rz = h[0];
-    } else {
-      if (lw.unfold_dot) {  // partials from the preconditioner's unfold
-        mdot_final<<<1, DOT_THREADS, 0, p->stream>>>(w.partial, ud.blocks, 2, w.out);
-        if ((e = hipGetLastError()) != hipSuccess ||
-            (e = hipMemcpyAsync(h, w.out, 2 * sizeof(double), hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
-            (e = hipStreamSynchronize(p->stream)) != hipSuccess)
-          return hip_fail(e, "sem_pcg_solve: dot");
-      } else if ((e = mdot(p, w, 2, w.r, w.z, w.z, w.q, h)) != hipSuccess) {
-        return hip_fail(e, "sem_pcg_solve: dot");
-      }
-      b = -a * h[1] / rz;
-      rz = h[0];
-    }
-    pcg_direction<<<gdir, 256, 0, p->stream>>>(w.p, w.z, b, n);
+    if (prec == SEM_F64) e = mdot(p, w, NEXT_RZ, w.r, w.z);
+    else if (lw.unfold_dot) e = scalars(p, w, ud.blocks, NEXT_RZ_ZQ);  // partials from the preconditioner's unfold
+    else e = mdot(p, w, NEXT_RZ_ZQ, w.r, w.z, w.z, w.q);
+    if (e != hipSuccess) return hip_fail(e, "sem_pcg_solve: dot");
+    pcg_direction<<<gdir, 256, 0, p->stream>>>(w.p, w.z, w.scal, n);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "sem_pcg_solve: direction");
   }
   if (tol > 0) return set_error(SEM_ENOCONV, "sem_pcg_solve: tolerance not met within max_iter");
