@@ -66,7 +66,7 @@ struct Coef {
 // Optional fused inner product of the weighted march: per-block partial sums of
 // <v, r>_M at partial[2 b] (partial == nullptr: none).
 struct DotOut {
-  const double *mx = nullptr, *my = nullptr, *mz = nullptr;
+  const double* mz = nullptr;
   double* partial = nullptr;
 };
 
@@ -156,7 +156,8 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
                                            const double* __restrict__ hx, const double* __restrict__ hy,
                                            const double* __restrict__ hz, int nx, int ny, int nz, int xchunk,
                                            int per, const Coef& c, int bx, int by, int bz,
-                                           double* __restrict__ lds, const DotOut& dot = DotOut()) {
+                                           double* __restrict__ lds, const double* __restrict__ mx = nullptr,
+                                           const double* __restrict__ my = nullptr, const DotOut& dot = DotOut()) {
   constexpr int BW = 2 * KH + 1;
   typedef TileGeo<KH, RW> G;
   constexpr int TY = G::TY;
@@ -192,6 +193,7 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
     if (wave == 0)
 #pragma unroll
       for (int d = 0; d < BW; ++d) czl[d * 64 + lane] = lok ? hz[(size_t)l * BW + d] : 0.0;
+    if (wave == 0) czl[BW * 64 + lane] = lok && dot.partial ? dot.mz[l] : 0.0;
   } else {
 #pragma unroll
     for (int d = 0; d < BW; ++d) cz[d] = lok ? hz[(size_t)l * BW + d] : 0.0;
@@ -233,7 +235,11 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
       const double x = v[in ? at(ii, q) : 0];
       w[q][d] = in ? x : 0.0;
     }
-  // prefetched operands of the current plane
+  // Prefetched operands of the current plane.  Vector memory answers in order, so any use
+  // of a value in the lambda, and any vector load between it and the next plane, waits for
+  // the whole prefetch: the weight's constant is added a plane later, the z masses of the
+  // fused dot lie in LDS, and the x and y masses come as restrict arguments (scalar loads).
+  // Weighted k = 5 march at 249^3: 177 -> 127 us.
   double hv[G::NH], fv[RW], dv[RW], wv[W ? RW : 1], wn[RW];
   auto prefetch = [&](int i) {  // halo and f/d of plane i, window front v[i + KH]
     const int ic = i < nx ? i : nx - 1;
@@ -251,7 +257,7 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
       wn[q] = in ? x : 0.0;
       fv[q] = (has_f && ok[q]) ? f[at(ic, q)] : 0.0;
       dv[q] = (has_d && ok[q]) ? dg[at(ic, q)] : 0.0;
-      if constexpr (W) wv[q] = ok[q] ? c.wa + wt[at(ic, q)] : 1.0;
+      if constexpr (W) wv[q] = ok[q] ? wt[at(ic, q)] : 0.0;
     }
   };
   const bool fuse = W && dot.partial != nullptr;  // uniform
@@ -269,7 +275,7 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
     for (int q = 0; q < RW; ++q) {
       fc[q] = fv[q];
       dc[q] = has_d ? dv[q] : w[q][KH];
-      if constexpr (W) dc[q] *= wv[q];
+      if constexpr (W) dc[q] *= c.wa + wv[q];
     }
     __syncthreads();  // the plane-i tile is complete (and plane i-2's readers are done)
     prefetch(i + 1);  // halo, f, d of plane i + 1 and the window front v[i + 1 + KH]
@@ -292,7 +298,7 @@ __device__ __forceinline__ void march_body(const double* __restrict__ v, const d
         put(r, row0 + l, o, rplane);
         zero_pad(r, row0, l, nz, ldr, rplane);
         if constexpr (W)
-          if (fuse) acc += (dot.mx[i] * dot.my[jr[q]] * dot.mz[l]) * (w[q][KH] * o);
+          if (fuse) acc += (mx[i] * my[jr[q]] * czl[BW * 64 + lane]) * (w[q][KH] * o);
       }
 #pragma unroll
       for (int d = 0; d + 1 < BW; ++d) w[q][d] = w[q][d + 1];
@@ -327,10 +333,11 @@ __global__ __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(march_waves<
 residual_march_kernel(const double* __restrict__ v, const double* __restrict__ f, const double* __restrict__ dg,
                       const double* __restrict__ wt, TR* __restrict__ r, int ldr, long rplane,
                       const double* __restrict__ hx, const double* __restrict__ hy, const double* __restrict__ hz,
-                      int nx, int ny, int nz, int xchunk, int per, Coef c, DotOut dot) {
-  __shared__ double lds[2 * TileGeo<KH, RW>::PLANE + (W ? (2 * KH + 1) * 64 : 0)];
+                      int nx, int ny, int nz, int xchunk, int per, Coef c, const double* __restrict__ mx,
+                      const double* __restrict__ my, DotOut dot) {
+  __shared__ double lds[2 * TileGeo<KH, RW>::PLANE + (W ? (2 * KH + 2) * 64 : 0)];
   march_body<KH, TR, W, RW>(v, f, dg, wt, r, ldr, rplane, hx, hy, hz, nx, ny, nz, xchunk, per, c, blockIdx.x,
-                        blockIdx.y, blockIdx.z, lds, dot);
+                        blockIdx.y, blockIdx.z, lds, mx, my, dot);
 }
 
 // Residuals of many solves (same k) in one launch: descriptor i owns blocks
@@ -424,14 +431,14 @@ void launch_march_rows(const ResidualArgs& ra, TR* r, const double* const hb[3],
   march_grid(dims, KH, &gx, &gy, &gz, &xchunk);
   auto run = [&](auto kernel, const double* wt, const DotOut& dot) {
     kernel<<<dim3(gx, gy, gz), dim3(RT), 0, stream>>>(ra.v, ra.f, ra.d, wt, r, ra.ldr, ra.rplane, hb[0], hb[1], hb[2],
-                                                      dims[0], dims[1], dims[2], xchunk, ra.periodic, c, dot);
+                                                      dims[0], dims[1], dims[2], xchunk, ra.periodic, c, ra.dot_mass[0], ra.dot_mass[1], dot);
   };
   // the per-node weight (an FP64 operator application of the variable-coefficient
   // solver) has its own instantiation, so that the others keep their registers
   if constexpr (std::is_same<TR, double>::value) {
     if (ra.wt) {
       DotOut dot;
-      if (ra.dot_partial) dot = DotOut{ra.dot_mass[0], ra.dot_mass[1], ra.dot_mass[2], ra.dot_partial};
+      if (ra.dot_partial) dot = DotOut{ra.dot_mass[2], ra.dot_partial};
       run(residual_march_kernel<KH, TR, true, RW>, ra.wt, dot);
       return;
     }
