@@ -10,7 +10,8 @@
 // multiple of 128 in both dimensions, so tile loads of G need no bounds checks
 // and padded contraction indices contribute exactly zero.
 //
-// Two tile shapes:
+// The solves take these kernels along axes past 1024 nodes (shorter ones run on strips
+// in LDS, mode_strip.hip), sem_mode_product always.  Two tile shapes:
 //   NN (q extent > 1: the x and y axes)  C = G^T-tile x X_p-tile
 //        GEMM rows = l (M = L), cols = q (N = Q), batch = p.
 //   NT (q extent = 1: the contiguous z axis)  C = X-tile x G-tile

@@ -4,10 +4,10 @@
 // representatives into the nrep symmetric modes and v-_r = x_r - x_R(r) of the nodd
 // pairs into the antisymmetric ones (forward), or e = S_sym c_sym and o = S_anti
 // c_anti into u_r = e_r + o_r, u_R(r) = e_r - o_r (backward).  The 128 x 128 tiles of
-// mode_f64.hip do the two halves in two launches, with fold passes between some
-// products and a read-back of e; at n = 31..512 most of their time is tile padding,
-// launches and the latency of short contractions.  Here a block owns a strip of 16
-// TC lines of the array along the contracted axis, folds it on its way into LDS,
+// mode_f64.hip do the two halves in two launches, with fold passes between some products
+// and a read-back of e; on short axes most of their time is tile padding, launches and
+// the latency of short contractions.  Here a block owns a strip of 16 TC lines of the
+// array along the contracted axis, folds it on its way into LDS,
 // and each wave multiplies it by TT tiles of 16 modes, both halves at once, so that
 //  * both halves, the fold and the unfold are one launch that reads and writes every
 //    value once, in place if wanted (a block reads its strip before it writes it);
@@ -16,8 +16,9 @@
 //  * small (y, z) planes do z and y in one launch: three launches for a solve.
 // The factors are not staged: a wave reads its fragments from L1 / L2 four contraction
 // steps ahead, in 1 KB pieces (an FP64 fragment pair feeds 2 TC MFMAs of 64 cycles).
-// What bounds them is the MFMA rate and the padding of the modes to 16; the strips'
-// loads and stores are overlapped by the other blocks of the CU.
+// What bounds them on long axes is the MFMA rate and the padding of the modes to 16; below
+// about 250 nodes the loads and stores of the strips as well, which the other blocks of a
+// CU hide only in part (192^3 FP64: 57 us a launch, 24 of bytes and 19 to 38 of MFMAs).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
