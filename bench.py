@@ -207,17 +207,16 @@ def bench_schrodinger(args, P, torch, dev, log):
     best = min(ok, key=lambda p: res["by_preconditioner"][p]["ms_per_solve"], default="f64")
     res.update({"preconditioner": best, **res["by_preconditioner"][best]})
     # the preconditioner's mode products dominate: their flop, 4 N (nx + ny + nz)
-    # per application (the products as defined; the reflection-split BF16 passes
+    # per application (the products as defined; the reflection-split products
     # execute half of it), over the whole solve time
     nx, ny, nz = plan.shape
     it_b = res["by_preconditioner"][best]["iterations"]
-    folded = best in ("bf16", "bf16x3")
     fd_flop = 4.0 * n * (nx + ny + nz) * (it_b + 1)
     ach = fd_flop / (res["by_preconditioner"][best]["ms_per_solve"] * 1e-3) / 1e12
     peak = {"f64": PEAK_FP64_TFLOPS, "f32": PEAK_FP32_TFLOPS}.get(best, PEAK_BF16_TFLOPS)
     res["roofline"] = {"bound": "mfma", "kernel": "whole PCG solve, preconditioner mode products counted",
                        "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
-                       "executed_frac": ach / peak / (2.0 if folded else 1.0)}
+                       "executed_frac": ach / peak / 2.0}
     res["tuned_shapes"] = plan.tuning(best) if best != "f64" else None
     del u, vd, fd, ued, plan
     torch.cuda.empty_cache()
@@ -480,14 +479,14 @@ def main() -> int:
         del ul
         peak = PEAK_FP32_TFLOPS if prec == "f32" else PEAK_BF16_TFLOPS
         # achieved counts the six mode products as defined, 4 N sum_a n_a flop per
-        # application; the BF16 modes run the reflection-split transforms, whose
-        # passes contract half-length blocks and execute 4 N sum_a nrep_a (nrep_a =
-        # orbit representatives of axis a, ~n_a / 2)
-        executed = folded_flops if prec != "f32" else fd_flops
+        # application; all run the reflection-split transforms, whose products contract
+        # half-length blocks and execute 4 N sum_a nrep_a (nrep_a = orbit
+        # representatives of axis a, ~n_a / 2)
+        executed = folded_flops
         ach = fd_flops / (fd_ms * 1e-3) / 1e12
         roof = {"bound": "mfma", "kernel": f"{prec} FD application: " +
                 ("fold + six reflection-split mode_rot_dma passes + unfold" if prec != "f32" else
-                 "six mode_rot_f32 passes"),
+                 "five launches of reflection-split strips"),
                 "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
                 "traffic": _traffic(prec), "traffic_detail": PROFILED_TRAFFIC.get(prec),
                 "launch_ms": fd_ms, "flops_per_launch": fd_flops, "executed_flops_per_launch": executed,
