@@ -197,9 +197,10 @@ sem_status sem_solve_lowp(sem_plan *p, sem_prec prec, const double *f, double *u
  * The low-precision mode products of a plan (sem_solve_refined, sem_solve_lowp,
  * the PCG preconditioner, the Cahn-Hilliard stepper, split-BF16 batch entries) run
  * with launch shapes chosen by timing on the first use of each precision: for
- * SEM_F32 the factor-tile rows (128, 96, 64 or 32) of each of the six passes (which
- * single solves take where an axis is longer than 1024 nodes; shorter axes run
- * products of fixed shape); for
+ * SEM_F32 the factor-tile rows (128, 96, 64 or 32) of each of the six rotating passes,
+ * which solves run where an axis is longer than 1024 nodes (with shorter axes they
+ * run products of fixed shape: a solve tunes nothing, the choices apply to
+ * sem_lowp_pass alone); for
  * SEM_BF16 / SEM_BF16X3 the tile order, g = 1, 2 or 4 column strips of 256 that
  * consecutive workgroups share, and the launch: one workgroup per tile (value g)
  * or one workgroup per compute unit looping over the tiles (value 16 + g).  The
@@ -213,7 +214,8 @@ sem_status sem_solve_lowp(sem_plan *p, sem_prec prec, const double *f, double *u
  * unreadable file counts as empty).  Nothing is timed while the plan stream is
  * capturing a graph: the shapes then follow the fixed rule until a later call
  * outside capture tunes them. */
-/* Tune prec now, consulting the cache (synchronous; uses the plan workspace).
+/* Tune prec now, consulting the cache (synchronous; uses the plan workspace; SEM_F32:
+ * the rotating passes, whether solves of the plan run them or not).
  * SEM_EINVAL: prec is SEM_F64 (no tunable shape) or the plan stream is capturing. */
 sem_status sem_plan_tune(sem_plan *p, sem_prec prec);
 /* The shapes of prec's six passes in order of application (choice[s] = 0 and
@@ -227,7 +229,8 @@ sem_status sem_tune_stats(int *hits, int *misses, int *entries);
 /* Launch pass `pass` (0..5, order of application; for the BF16 modes the passes
  * of the reflection-split sequence) of prec's FD application `reps` times on the
  * plan stream, with the plan's tuned shapes, on whatever the plan workspace holds:
- * a way to time the mode-product kernels one by one (events around the call).
+ * a way to time the passes one by one (events around the call).  SEM_F32: the
+ * rotating passes, which solves run where an axis is longer than 1024 nodes.
  * The result is not meaningful by itself; run a solve of prec first for
  * realistic data. Every access stays inside the workspace and the factors
  * whatever they hold. SEM_F32's last pass runs as an FP32 store of the same
@@ -359,7 +362,9 @@ sem_status sem_ch_dims(const sem_ch *c, int n[3]);
  * own stream. */
 sem_status sem_ch_set_stream(sem_ch *c, void *hip_stream);
 /* Launch shapes of the stepper's mode products, tuned at creation (see
- * sem_plan_tune; *tuned = 0 for SEM_F64). */
+ * sem_plan_tune; *tuned = 0 for SEM_F64).  A SEM_F32 stepper with axes of up to 1024
+ * nodes runs products of fixed shape and times nothing: the rows are those that the
+ * rotating passes would take untimed. */
 sem_status sem_ch_tuning(const sem_ch *c, int *tuned, int choice[6]);
 /* enable = 1 (default): each step is a replay of a captured HIP graph (captured on
  * the first call, and again whenever phi_n / phi_nm1 change address); 0: the same

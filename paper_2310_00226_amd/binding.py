@@ -267,7 +267,8 @@ class Plan:
         return self.tuning(pv)
 
     def tuning(self, prec: str = "bf16x3"):
-        """The shapes of prec's six passes (sem_plan_tuning), or None before tuning."""
+        """The shapes of prec's six passes (sem_plan_tuning), or None before tuning (which
+        an FP32 solve with axes of up to 1024 nodes does not do: it runs none of them)."""
         pv = PRECISIONS[prec] if isinstance(prec, str) else int(prec)
         tuned = c_int(0)
         ch = (c_int * 6)()

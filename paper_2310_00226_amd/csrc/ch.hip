@@ -267,7 +267,12 @@ sem_status sem_ch_tuning(const sem_ch* c, int* tuned, int choice[6]) {
     for (int s = 0; s < 6; ++s) choice[s] = 0;
     return SEM_OK;
   }
-  return sem_plan_tuning(c->plan, c->prec, tuned, choice);
+  const sem_status st = sem_plan_tuning(c->plan, c->prec, tuned, choice);
+  if (st != SEM_OK || *tuned || c->prec != SEM_F32) return st;
+  // FP32 on strips: nothing is timed, the rotating passes would go by the rule
+  for (int s = 0; s < 6; ++s) choice[s] = lp_rule_rows(c->plan->dims[2 - s % 3]);
+  *tuned = 1;
+  return SEM_OK;
 }
 
 sem_status sem_ch_set_stream(sem_ch* c, void* s) {

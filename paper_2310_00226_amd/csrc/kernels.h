@@ -223,6 +223,9 @@ struct LpPass {
 constexpr int DMA_PERSIST = 16;
 // FP32 passes (mode_lp.hip): mode LP_F32, in_kind 0 or 1, out_kind 1 or 0 (accumulate).
 hipError_t launch_mode_lp(const LpPass& ps, hipStream_t stream);
+// Factor-tile rows of a pass of L output modes that was not tuned: 96 where they cover L
+// with clearly fewer padded rows than 128 (e.g. L = 257: 288 rows instead of 384).
+int lp_rule_rows(int L);
 
 // One FP32 pass of one solve inside a batched (persistent) launch: the fields of
 // LpPass plus the tile bookkeeping.  Descriptor i owns tiles [tile0, tile0 +

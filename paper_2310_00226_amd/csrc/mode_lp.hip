@@ -354,6 +354,11 @@ bool lp_kind_ok(int in_kind, int out_kind, int epi) {
   return out_kind == 1 && epi != EPI_ACCUM && (in_kind == 0 || in_kind == 1);
 }
 
+int lp_rule_rows(int L) {
+  const long r128 = (L + 127) / 128 * 128, r96 = (L + 95) / 96 * 96;
+  return r96 * 10 < r128 * 9 ? 96 : 128;
+}
+
 hipError_t launch_mode_lp(const LpPass& ps, hipStream_t stream) {
   if (ps.mode != LP_F32 || !lp_kind_ok(ps.in_kind, ps.out_kind, ps.epi_kind)) return hipErrorInvalidValue;
   LpDesc d;
@@ -370,8 +375,6 @@ hipError_t launch_mode_lp(const LpPass& ps, hipStream_t stream) {
   d.L = ps.L;
   d.ldf = ps.ldf;
   using namespace f32k;
-  // a tuned tile shape, else 96-row factor tiles when they cover L with clearly
-  // fewer padded rows (e.g. L = 257: 288 rows instead of 384)
   switch (ps.tile_rows) {
     case 128: return launch_single_tile<T128>(d, ps, stream);
     case 96: return launch_single_tile<T96>(d, ps, stream);
@@ -379,8 +382,7 @@ hipError_t launch_mode_lp(const LpPass& ps, hipStream_t stream) {
     case 32: return launch_single_tile<T32>(d, ps, stream);
     default: break;
   }
-  const long r128 = (ps.L + 127) / 128 * 128, r96 = (ps.L + 95) / 96 * 96;
-  if (r96 * 10 < r128 * 9) return launch_single_tile<T96>(d, ps, stream);
+  if (lp_rule_rows(ps.L) == 96) return launch_single_tile<T96>(d, ps, stream);
   return launch_single_tile<T128>(d, ps, stream);
 }
 

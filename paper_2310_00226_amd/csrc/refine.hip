@@ -254,7 +254,10 @@ sem_status lp_check(const sem_plan* p, sem_prec prec) {
 }
 
 // Low-precision factors and the plan workspace laid out for prec; with tune, the
-// launch shapes of prec are tuned (once per plan, see lp_tune).
+// launch shapes of the products that a solve in prec runs are tuned (once per plan, see
+// lp_tune).  FP32 solves on strips have none: timing the rotating passes, which they do
+// not run, cost the first FP32 call of a plan 96 launches of dense products (first refined
+// solve with / without: 511^3 64.6 / 21.9 ms, 999^3 819 / 221).
 sem_status lp_prepare(sem_plan* p, sem_prec prec, LpWork* w, bool tune) {
   sem_status st = lp_check(p, prec);
   if (st != SEM_OK) return st;
@@ -264,7 +267,7 @@ sem_status lp_prepare(sem_plan* p, sem_prec prec, LpWork* w, bool tune) {
   st = plan_workspace(p, workspace_need(p, prec), &ws);
   if (st != SEM_OK) return st;
   st = lp_layout(p, prec, ws, w);
-  if (st != SEM_OK || !tune) return st;
+  if (st != SEM_OK || !tune || (prec == SEM_F32 && f32_strips(p))) return st;
   return lp_tune(p, *w);
 }
 
@@ -870,7 +873,8 @@ extern "C" sem_status sem_plan_tune(sem_plan* p, sem_prec prec) {
   if (cap != hipStreamCaptureStatusNone) return set_error(SEM_EINVAL, "sem_plan_tune: the plan stream is capturing");
   p->tuned[prec] = 0;
   LpWork w;
-  sem_status st = lp_prepare(p, prec, &w, true);
+  sem_status st = lp_prepare(p, prec, &w, false);
+  if (st == SEM_OK) st = lp_tune(p, w);
   if (st != SEM_OK) return st;
   if ((e = hipStreamSynchronize(p->stream)) != hipSuccess) return hip_fail(e, "sem_plan_tune");
   return SEM_OK;
@@ -915,7 +919,8 @@ extern "C" sem_status sem_lowp_pass(sem_plan* p, sem_prec prec, int pass, int re
     return set_error(SEM_EINVAL, "sem_lowp_pass: only SEM_F32, SEM_BF16 and SEM_BF16X3 run low-precision passes");
   if (pass < 0 || pass > 5 || reps < 1) return set_error(SEM_EINVAL, "sem_lowp_pass: pass in 0..5, reps >= 1");
   LpWork w;
-  sem_status st = lp_prepare(p, prec, &w, true);
+  sem_status st = lp_prepare(p, prec, &w, false);
+  if (st == SEM_OK) st = lp_tune(p, w);
   if (st != SEM_OK) return st;
   const Spectral sp{p->alpha, 1.0, 0.0};
   const LpPass ps = prec == SEM_F32 ? f32_pass(p, w, sp, pass, nullptr, nullptr, 1, nullptr) : folded_pass(p, w, sp, pass);
