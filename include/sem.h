@@ -302,7 +302,8 @@ typedef struct sem_batch sem_batch;
  * the batch), the first uses the plan's.  The plans are not owned and must
  * outlive the batch.  Creation prepares the FP32 factors and workspaces of every
  * entry, then times the candidate tile shapes of the FP32 mode-product kernel on
- * the batch's own passes and keeps the fastest per contraction-length bucket
+ * the batch's own passes (of the problems that its persistent launches run, see
+ * sem_batch_solve) and keeps the fastest per contraction-length bucket
  * (through the tuning cache of sem_plan_tune: a bucket of the same length and
  * log2 work found there is not timed again).
  * Synchronous.  SEM_EINVAL: count < 1, a null plan, k > 8, plans on different
@@ -311,7 +312,7 @@ sem_status sem_batch_create(int count, sem_plan *const *plans, sem_batch **out);
 void sem_batch_destroy(sem_batch *b);
 sem_status sem_batch_set_stream(sem_batch *b, void *hip_stream);
 /* Block-tile rows chosen per contraction-length bucket n <= 16, 32, 64, 128, 256,
- * > 256 (0 = no such length in the batch). */
+ * > 256 (0 = no such length among the problems of the persistent launches). */
 sem_status sem_batch_tile_rows(const sem_batch *b, int rows[6]);
 /* Solve all problems: f[i], u[i] are device arrays of plan i's N_i doubles (host
  * arrays of count device pointers; u[i] must not alias f[i]).

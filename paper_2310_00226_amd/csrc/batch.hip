@@ -261,9 +261,20 @@ hipError_t run_variant(sem_batch* b, int v) {
   return hipSuccess;
 }
 
-// Time the candidate tile shapes on the batch's own forward-y passes, per bucket.
+// Whether an FP32 solve of p runs by itself on a side stream.
+bool solo_f32(const sem_plan* p) { return p->N >= SOLO_MIN_N && f32_strips(p); }
+
+// Time the candidate tile shapes on the batch's own passes, per bucket: those of the
+// solves that the persistent launches run (with 16 problems of 8..64 elements per axis 9
+// run solo and would bring 99% of the timed work), one launch per axis as in a solve (all
+// three in one fill the chip with larger tiles than a pass has).  From the longest bucket
+// to the shortest, which take a shape already in use where none is 10% faster.
+// FP32 / BF16X3 solve in ms with every solve in one timed launch / this: 24 problems of
+// 5..14 elements and 6 of 30..50 5.41 / 5.28 -> 5.30 / 5.21, 40 of 8..30 4.55 / 4.76 ->
+// 4.02 / 4.49, 64 of 8..20 and 2 of 40..60 9.87 / 9.70 -> 9.53 / 9.55; creation 63, 47,
+// 89 -> 38, 34, 57.
 sem_status autotune(sem_batch* b) {
-  // descriptors: a forward pass along every axis of every solve, FP32 in and out
+  // descriptors: a forward pass along every axis of these solves, FP32 in and out
   // inside the solve's own workspace (contents irrelevant for timing)
   std::vector<int> ones(b->count, 1);
   hipError_t e = hipMemcpy(b->d_active, ones.data(), ones.size() * sizeof(int), hipMemcpyHostToDevice);
@@ -272,52 +283,64 @@ sem_status autotune(sem_batch* b) {
   if ((e = hipEventCreate(&t0)) != hipSuccess || (e = hipEventCreate(&t1)) != hipSuccess)
     return hip_fail(e, "sem_batch: autotune events");
   sem_status st = SEM_OK;
-  for (int bk = 0; bk < NBUCKET && st == SEM_OK; ++bk) {
+  for (int bk = NBUCKET - 1; bk >= 0 && st == SEM_OK; --bk) {
     std::vector<LpDesc> base;
+    int first[4] = {0, 0, 0, 0};  // descriptors of one axis, a launch each as in a solve
     long work = 0;
-    for (int i = 0; i < b->count; ++i)
-      for (int s : {1, 2, 3}) {  // variants 2, 3, 4 = passes along y, x, z
-        LpDesc d = make_desc(b, i, s + 1, nullptr, nullptr);
+    for (int a = 0; a < 3; ++a) {  // variants 2, 3, 4 = passes along y, x, z
+      for (int i = 0; i < b->count; ++i) {
+        if (solo_f32(b->plans[i])) continue;
+        LpDesc d = make_desc(b, i, a + 2, nullptr, nullptr);
         if (bucket_of(d.L) != bk) continue;
         d.epi = EpiLP();
         base.push_back(d);
         work += d.P * (long)d.L;
       }
+      first[a + 1] = (int)base.size();
+    }
     if (base.empty()) continue;
     // the tuning cache holds the choice per device, length bucket and log2 of the
-    // bucket's work (rows x length summed over its passes)
+    // bucket's work (rows x length summed over its passes).  "axis": timed a launch per
+    // axis; choices kept in older cache files under "batch_f32" are not read
     char key[128];
-    std::snprintf(key, sizeof(key), "%s|batch_f32|Lb%d|W%d", b->arch, bk, tune_bucket(work));
+    std::snprintf(key, sizeof(key), "%s|batch_f32_axis|Lb%d|W%d", b->arch, bk, tune_bucket(work));
     int cached = 0;
     if (tune_lookup(key, &cached)) {
       b->tile_rows[bk] = cached;
       continue;
     }
-    float best = INFINITY;
-    int best_tr = 128;
+    float best = INFINITY, best_used = INFINITY;
+    int best_tr = 128, used_tr = 0;  // of all candidates, of those that another bucket took
     for (int tr : TILE_CANDIDATES) {
       std::vector<LpDesc> ds = base;
-      long tiles = 0;
-      for (LpDesc& d : ds) {
-        d.tiles_l = (d.L + tr - 1) / tr;
-        d.tile0 = tiles;
-        tiles += (long)d.tiles_l * ((d.P + 127) / 128);
-      }
+      long tiles[3] = {0, 0, 0};
+      for (int a = 0; a < 3; ++a)
+        for (int q = first[a]; q < first[a + 1]; ++q) {
+          LpDesc& d = ds[q];
+          d.tiles_l = (d.L + tr - 1) / tr;
+          d.tile0 = tiles[a];
+          tiles[a] += (long)d.tiles_l * ((d.P + 127) / 128);
+        }
       if ((e = hipMemcpy(b->d_desc, ds.data(), ds.size() * sizeof(LpDesc), hipMemcpyHostToDevice)) != hipSuccess) {
         st = hip_fail(e, "sem_batch: autotune upload");
         break;
       }
       const int grid = b->cus * lp_batch_blocks_per_cu(tr);
-      // one warm-up launch, then the fastest of TUNE_REPS timed launches (the small
+      auto run = [&]() {
+        hipError_t r = hipSuccess;
+        for (int a = 0; a < 3 && r == hipSuccess; ++a)
+          r = launch_mode_f32_batch(1, 1, EPI_STORE, tr, b->d_desc + first[a], first[a + 1] - first[a], tiles[a],
+                                    b->d_active, grid, b->stream);
+        return r;
+      };
+      // one warm-up run, then the fastest of TUNE_REPS timed ones (the small
       // buckets run for microseconds, where single timings are noisy)
       float ms = INFINITY;
-      e = launch_mode_f32_batch(1, 1, EPI_STORE, tr, b->d_desc, (int)ds.size(), tiles, b->d_active, grid, b->stream);
+      e = run();
       for (int rep = 0; rep < TUNE_REPS && e == hipSuccess; ++rep) {
         float one = 0.f;
         e = hipEventRecord(t0, b->stream);
-        if (e == hipSuccess)
-          e = launch_mode_f32_batch(1, 1, EPI_STORE, tr, b->d_desc, (int)ds.size(), tiles, b->d_active, grid,
-                                    b->stream);
+        if (e == hipSuccess) e = run();
         if (e == hipSuccess) e = hipEventRecord(t1, b->stream);
         if (e == hipSuccess) e = hipEventSynchronize(t1);
         if (e == hipSuccess) e = hipEventElapsedTime(&one, t0, t1);
@@ -331,7 +354,13 @@ sem_status autotune(sem_batch* b) {
         best = ms;
         best_tr = tr;
       }
+      if (ms < best_used && std::count(b->tile_rows, b->tile_rows + NBUCKET, tr)) {
+        best_used = ms;
+        used_tr = tr;
+      }
     }
+    // every tile shape in use is a launch more in each pass
+    if (used_tr && best_used <= 1.1f * best) best_tr = used_tr;
     b->tile_rows[bk] = best_tr;
     tune_store(key, best_tr);
   }
@@ -535,7 +564,7 @@ sem_status sem_batch_solve(sem_batch* b, sem_prec prec, double tol, int max_iter
   for (int i = 0; i < n; ++i) {
     const int* d = b->plans[i]->dims;
     const bool split = prec == SEM_BF16X3 && std::min({d[0], d[1], d[2]}) >= SPLIT_MIN_DIM;
-    solo[i] = split || (b->plans[i]->N >= SOLO_MIN_N && f32_strips(b->plans[i]));
+    solo[i] = split || solo_f32(b->plans[i]);
     sem_status st = prepare_entry(b, i, split ? SEM_BF16X3 : SEM_F32);
     if (st != SEM_OK) return st;
   }

@@ -46,3 +46,23 @@ def test_f32_solves_past_the_strips_are_tuned(torch, P):
     f = torch.from_numpy(normal_noise(plan.shape, seed=6)).cuda()
     plan.solve_lowp(f, prec="f32")
     assert set(plan.tuning("f32")) <= {128, 96, 64, 32}
+
+
+def test_batch_tunes_the_problems_of_its_persistent_launches(torch, P):
+    """A problem that runs by itself (10^6 unknowns) has no part in their tile rows."""
+    small = [P.Plan(3, (6, 7, 5), BOX, 1.0, "dirichlet"), P.Plan(2, (40, 33, 30), BOX, 2.0, "dirichlet")]
+    big = P.Plan(4, (26, 27, 26), BOX, 1.0, "dirichlet")
+    rows, before = P.Batch(small).tile_rows(), P.tune_stats()
+    both = P.Batch(small + [big])
+    after = P.tune_stats()
+    assert both.tile_rows() == rows
+    assert after["misses"] == before["misses"] and after["entries"] == before["entries"], (before, after)
+    alone = P.Batch([big, big])
+    assert alone.tile_rows() == [0] * 6 and P.tune_stats() == after
+    for batch, plans in ((both, small + [big]), (alone, [big, big])):
+        fs = [torch.from_numpy(normal_noise(p.shape, seed=40 + i)).cuda() for i, p in enumerate(plans)]
+        us = [torch.empty_like(f) for f in fs]
+        assert batch.solve(fs, us, prec="f32", tol=1e-12)[1] == 0
+        for p, f, u in zip(plans, fs, us):
+            want = p.solve(f)
+            assert float((u - want).abs().max()) <= 1e-10 * float(want.abs().max())
