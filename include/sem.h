@@ -206,8 +206,8 @@ sem_status sem_solve_lowp(sem_plan *p, sem_prec prec, const double *f, double *u
  * or one workgroup per compute unit looping over the tiles (value 16 + g).  The
  * timed candidates are 1, 4, 17 and 20.  The shapes change no result bit.  Each candidate is launched
  * once untimed, then three times, on the plan's own workspace; the fastest is kept
- * in the plan and in a process-wide cache keyed by device architecture, kernel,
- * output layout and log2 size buckets of the pass, which later plans of similar
+ * in the plan and in a process-wide cache keyed by device architecture, kernel, block
+ * tile (BF16 modes), output layout and log2 size buckets of the pass, which later plans of similar
  * size read instead of timing.  With the environment variable SEM_TUNE_CACHE
  * naming a file, the cache is read from it on first use and rewritten after each
  * new entry (JSON: {"version": 1, "entries": {"<key>": <choice>, ...}}; an

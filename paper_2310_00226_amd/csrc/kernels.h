@@ -256,6 +256,8 @@ int lp_batch_blocks_per_cu(int tile_rows);
 // planes (out_kind 2, any column layout, STORE or DIVIDE) or FP32 (out_kind 1,
 // COL_PLAIN, STORE).  Padding columns receive finite values.
 bool dma_supported(const LpPass& ps);
+// Rows of the block tile that launch_mode_dma takes for ps: 256, 128 or 64.
+int dma_tile_rows(const LpPass& ps);
 hipError_t launch_mode_dma(const LpPass& ps, hipStream_t stream);
 // Reflection split of one axis: nrep orbit representatives (v+ at columns
 // [0, pad), v- at [pad, 2 pad) of a folded row), reflection n - 1 - r or, per,

@@ -808,12 +808,12 @@ bool dma_supported(const LpPass& ps) {
 }
 
 // Tiles of a pass along l (both blocks) and p.
-template <class G, int COL>
+template <class G>
 static void dma_tiles(const LpPass& ps, long* tl1, long* tiles_l, long* tiles_p) {
   *tl1 = (ps.L + G::BM - 1) / G::BM;
   *tiles_l = *tl1 + (ps.K2 > 0 ? (ps.L2 + G::BM - 1) / G::BM : 0);
-  *tiles_p = COL == COL_FOLD ? (long)ps.A * ((ps.bsym + G::BN / 2 - 1) / (G::BN / 2))
-                             : ((long)ps.A * ps.ldy + G::BN - 1) / G::BN;
+  *tiles_p = ps.col == COL_FOLD ? (long)ps.A * ((ps.bsym + G::BN / 2 - 1) / (G::BN / 2))
+                                : ((long)ps.A * ps.ldy + G::BN - 1) / G::BN;
 }
 
 template <int MODE, class TOut, int EPI, int COL, class G>
@@ -845,7 +845,7 @@ static hipError_t launch_dma_g(const LpPass& ps, hipStream_t stream) {
   g.bn = ps.bn;
   g.bper = ps.bper;
   g.epi = ps.epi;
-  dma_tiles<G, COL>(ps, &g.tl1, &g.tiles_l, &g.tiles_p);
+  dma_tiles<G>(ps, &g.tl1, &g.tiles_l, &g.tiles_p);
   g.ntiles = g.tiles_l * g.tiles_p;
   // tile_group: g in {1, 2, 4} (one block per tile) or DMA_PERSIST + g (one block
   // per CU looping over the tiles)
@@ -877,20 +877,28 @@ static hipError_t launch_dma_g(const LpPass& ps, hipStream_t stream) {
 // the 256 / 128 / 64-row tile everywhere: 119^3 92 / 49 / 41 us, 191^3 210 / 118 / 113,
 // (257, 311, 227) 435 / 300 / 277, 299^3 516 / 469 / 406, 511^3 1784 / 2041 / 2204.
 // Every output element is summed in the same order by all three.
-template <class G, int COL>
+template <class G>
 static long dma_cost(const LpPass& ps, long weight) {
   long tl1, tiles_l, tiles_p;
-  dma_tiles<G, COL>(ps, &tl1, &tiles_l, &tiles_p);
+  dma_tiles<G>(ps, &tl1, &tiles_l, &tiles_p);
   return (tiles_l * tiles_p + 255) / 256 * (G::BM * G::BN / 8192) * weight;
+}
+
+int dma_tile_rows(const LpPass& ps) {
+  using namespace dmak;
+  const long c256 = dma_cost<T256>(ps, 20), c128 = dma_cost<T128>(ps, 24), c64 = dma_cost<T64>(ps, 27);
+  if (c256 <= c128 && c256 <= c64) return 256;
+  return c128 <= c64 ? 128 : 64;
 }
 
 template <int MODE, class TOut, int EPI, int COL>
 static hipError_t launch_dma_t(const LpPass& ps, hipStream_t stream) {
   using namespace dmak;
-  const long c256 = dma_cost<T256, COL>(ps, 20), c128 = dma_cost<T128, COL>(ps, 24), c64 = dma_cost<T64, COL>(ps, 27);
-  if (c256 <= c128 && c256 <= c64) return launch_dma_g<MODE, TOut, EPI, COL, T256>(ps, stream);
-  if (c128 <= c64) return launch_dma_g<MODE, TOut, EPI, COL, T128>(ps, stream);
-  return launch_dma_g<MODE, TOut, EPI, COL, T64>(ps, stream);
+  switch (dma_tile_rows(ps)) {
+    case 256: return launch_dma_g<MODE, TOut, EPI, COL, T256>(ps, stream);
+    case 128: return launch_dma_g<MODE, TOut, EPI, COL, T128>(ps, stream);
+    default: return launch_dma_g<MODE, TOut, EPI, COL, T64>(ps, stream);
+  }
 }
 
 template <int MODE>

@@ -550,8 +550,8 @@ hipError_t lp_fd(sem_plan* p, const LpWork& w, const Spectral& sp, const double*
 // of 1 or 4 p-strips, with one block per tile or one block per CU looping over
 // the tiles (DMA_PERSIST + group).  Each pass geometry is timed once (one warm-up launch, the
 // fastest of three), on the plan's own workspace, and the choice is kept in the
-// plan and in the tuning cache (key: architecture, kernel, output layout, and
-// log2 buckets of rows, contraction length and tensor rows), so plans of similar
+// plan and in the tuning cache (key: architecture, kernel with its block tile, output
+// layout, and log2 buckets of rows, contraction length and tensor rows), so plans of similar
 // size skip the timing, also in later processes with SEM_TUNE_CACHE.
 static const char* arch_name(const sem_plan* p) {
   static thread_local char name[64];
@@ -565,9 +565,11 @@ static const char* arch_name(const sem_plan* p) {
 
 static std::string pass_key(const sem_plan* p, const LpPass& ps) {
   char buf[192];
-  std::snprintf(buf, sizeof(buf), "%s|%s|epi%d|col%d|out%d|L%d|K%d|P%d", arch_name(p),
-                ps.mode == LP_F32 ? "f32" : ps.mode == LP_BF16 ? "bf16" : "bf16x3", ps.epi_kind, ps.col,
-                ps.out_kind, tune_bucket(ps.L + ps.L2), tune_bucket(ps.K), tune_bucket(ps.P));
+  const int len = std::snprintf(buf, sizeof(buf), "%s|%s|epi%d|col%d|out%d|L%d|K%d|P%d", arch_name(p),
+                                ps.mode == LP_F32 ? "f32" : ps.mode == LP_BF16 ? "bf16" : "bf16x3", ps.epi_kind,
+                                ps.col, ps.out_kind, tune_bucket(ps.L + ps.L2), tune_bucket(ps.K), tune_bucket(ps.P));
+  // the passes of one bucket take different block tiles, other kernels with orders of their own
+  if (ps.mode != LP_F32) std::snprintf(buf + len, sizeof(buf) - len, "|t%d", dma_tile_rows(ps));
   return buf;
 }
 

@@ -1,5 +1,10 @@
 """Launch-shape tuning where several routes exist: only kernels that the solves run are
 timed, and their choices are kept apart by route (needs an MI355X)."""
+import json
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -7,6 +12,7 @@ from workloads import normal_noise
 
 pytestmark = pytest.mark.gpu
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 BOX = (-1, 1, -1, 1, -1, 1)
 
 
@@ -66,3 +72,29 @@ def test_batch_tunes_the_problems_of_its_persistent_launches(torch, P):
         for p, f, u in zip(plans, fs, us):
             want = p.solve(f)
             assert float((u - want).abs().max()) <= 1e-10 * float(want.abs().max())
+
+
+_CHILD = r"""
+import json, sys
+sys.path.insert(0, {root!r})
+import torch
+import paper_2310_00226_amd as P
+out = []
+for ne in ((72, 37, 130), (67, 36, 177)):
+    P.Plan(1, ne, (-1, 1) * 3, 1.0, "dirichlet").tune("bf16x3")
+    out.append(P.tune_stats())
+print("RESULT " + json.dumps(out), flush=True)
+"""
+
+
+def test_bf16_choices_are_kept_per_block_tile(torch, P, tmp_path):
+    """Two plans in the same size buckets; the first pass of the second takes 128-row
+    tiles, everything else 64-row ones: its choice is its own."""
+    path = tmp_path / "tune.json"
+    r = subprocess.run([sys.executable, "-c", _CHILD.format(root=ROOT)], env=dict(os.environ, SEM_TUNE_CACHE=str(path)),
+                       capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    first, second = json.loads(r.stdout.split("RESULT ")[1])
+    assert first["misses"] == 6 and second["misses"] == 7 and second["hits"] == 5, (first, second)
+    tiles = sorted(key.rsplit("|", 1)[1] for key in json.loads(path.read_text())["entries"])
+    assert tiles == ["t128"] + ["t64"] * 6
