@@ -32,7 +32,8 @@ struct sem_plan {
   double* d_gff[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
   double* d_gbf[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
   int fld[3] = {0, 0, 0};
-  double* d_gst[3] = {nullptr, nullptr, nullptr};  // the same blocks in strip order (strip_pack_axis)
+  // the same blocks in strip order (strip_pack_axis); an axis has one or the other (f64_strip)
+  double* d_gst[3] = {nullptr, nullptr, nullptr};
   double* d_lamf64[3] = {nullptr, nullptr, nullptr};  // eigenvalues in folded mode order (FP64 path)
   // low-precision factors (created on first use): [axis][0 = forward, 1 = backward],
   // layout [l][k], zero-padded to lp_ld x lp_ld
@@ -102,6 +103,9 @@ hipError_t lp_fd(sem_plan* p, const LpWork& w, const Spectral& sp, const double*
                  unsigned long long* norms);
 // Whether the FP32 products of a plan run on strips (every axis up to 1024 nodes).
 bool f32_strips(const sem_plan* p);
+// Whether the FP64 products along axis a run on strips (the axis up to 1024 nodes; along x
+// also planes of up to STRIP_MAX_Q nodes), else on the tiles of mode_f64.hip.
+bool f64_strip(const sem_plan* p, int a);
 // FP64 FD application u = S_3 [g(L) (F_3 f)] on the reflection-split transforms
 // (tmp: N doubles; u may alias f).
 hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, double* tmp);

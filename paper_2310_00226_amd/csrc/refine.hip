@@ -406,6 +406,10 @@ static void strip_factors(const T* g, int nrep, const void** fs, const void** fa
   *ba = g + 3 * block;
 }
 
+bool f64_strip(const sem_plan* p, int a) {
+  return strip_axis_ok(strip_axis(p, a), sizeof(double)) && (a > 0 || (long)p->dims[1] * p->dims[2] <= STRIP_MAX_Q);
+}
+
 bool f32_strips(const sem_plan* p) {
   for (int a = 0; a < 3; ++a)
     if (!strip_axis_ok(strip_axis(p, a), sizeof(float))) return false;
@@ -669,7 +673,7 @@ hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, dou
   EpiArgs none, plus_z, minus_z, unfold[3];
   for (int a = 0; a < 3; ++a) {
     ax[a] = strip_axis(p, a);
-    strip[a] = strip_axis_ok(ax[a], sizeof(double)) && (a > 0 || QX <= STRIP_MAX_Q);
+    strip[a] = f64_strip(p, a);
     unfold[a].rn = ax[a].n;
     unfold[a].rper = unfold[a].roff = ax[a].per;
   }
@@ -692,9 +696,10 @@ hipError_t fd64(sem_plan* p, const Spectral& sp, const double* f, double* u, dou
   const int epi = sp.kind ? EPI_SPECTRAL : EPI_DIVIDE;
   // antisymmetric blocks of the tiles: forward factors start at row off
   // (representative off), backward factors at column off
-  const double* gfa[3];
-  const double* gba[3];
+  const double* gfa[3] = {};
+  const double* gba[3] = {};
   for (int a = 0; a < 3; ++a) {
+    if (strip[a]) continue;
     gfa[a] = p->d_gff[a][1] + (size_t)ax[a].per * p->fld[a];
     gba[a] = p->d_gbf[a][1] + ax[a].per;
   }

@@ -65,16 +65,23 @@ static hipError_t upload_vec(const std::vector<double>& v, double** dst) {
   return hipMemcpy(*dst, v.data(), sizeof(double) * v.size(), hipMemcpyHostToDevice);
 }
 
-// Reflection-split FP64 factors of axis a in the G[m][l] = A[l][m] layout of the
-// FP64 kernels, fld columns (nrep rounded up to 128) and fld + 128 zero-padded
+// Reflection-split FP64 factors of axis a for the kernels that its products run, and the
+// folded eigenvalues.  Strips: in fragment order.  Tiles: in the G[m][l] = A[l][m] layout
+// of the FP64 kernels, fld columns (nrep rounded up to 128) and fld + 128 zero-padded
 // rows, so that a block read at a row or column offset of one (the antisymmetric
 // blocks skip the representatives that are their own reflection) keeps whole
 // tiles inside: forward blocks A = (symmetric or antisymmetric modes) x
-// representatives, backward blocks A = representatives x (modes of the block);
-// and the folded eigenvalues.
+// representatives, backward blocks A = representatives x (modes of the block).
 static hipError_t upload_fold_factors(sem_plan* p, int a) {
   const semfd::AxisData& ax = p->ax[a];
   const int nr = ax.nrep, no = ax.nodd, ld = ((nr + 127) / 128) * 128;
+  const hipError_t el = upload_vec(ax.lam_fold, &p->d_lamf64[a]);
+  if (el != hipSuccess) return el;
+  if (f64_strip(p, a)) {
+    std::vector<double> st(4 * strip_pack_elems<double>(nr), 0.0);
+    strip_pack_axis(ax.ffold.data(), ax.bfold_sym.data(), ax.bfold_anti.data(), nr, no, st.data());
+    return upload_vec(st, &p->d_gst[a]);
+  }
   p->fld[a] = ld;
   std::vector<double> g[4];
   for (auto& v : g) v.assign((size_t)(ld + 128) * ld, 0.0);
@@ -96,13 +103,7 @@ static hipError_t upload_fold_factors(sem_plan* p, int a) {
     if ((e = hipMemcpy(*dst[i], g[i].data(), sizeof(double) * g[i].size(), hipMemcpyHostToDevice)) != hipSuccess)
       return e;
   }
-  if (strip_axis_ok(StripAxis{ax.n, nr, no, 0}, sizeof(double))) {
-    std::vector<double> st(4 * strip_pack_elems<double>(nr), 0.0);
-    strip_pack_axis(ax.ffold.data(), ax.bfold_sym.data(), ax.bfold_anti.data(), nr, no, st.data());
-    const hipError_t e = upload_vec(st, &p->d_gst[a]);
-    if (e != hipSuccess) return e;
-  }
-  return upload_vec(ax.lam_fold, &p->d_lamf64[a]);
+  return hipSuccess;
 }
 
 sem_status plan_workspace(sem_plan* p, size_t need, void** out) {
