@@ -35,11 +35,9 @@ struct sem_plan {
   // the same blocks in strip order (strip_pack_axis); an axis has one or the other (f64_strip)
   double* d_gst[3] = {nullptr, nullptr, nullptr};
   double* d_lamf64[3] = {nullptr, nullptr, nullptr};  // eigenvalues in folded mode order (FP64 path)
-  // low-precision factors (created on first use): [axis][0 = forward, 1 = backward],
+  // dense FP32 factors (created on first use): [axis][0 = forward, 1 = backward],
   // layout [l][k], zero-padded to lp_ld x lp_ld
   void* lp_f32[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
-  void* lp_hi[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
-  void* lp_lo[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
   int lp_ld[3] = {0, 0, 0};
   // reflection-split BF16 factors (hi plane, then lo plane lpf_plane elements
   // later) [axis][0 = forward, 1 = backward]: forward rows = symmetric modes from 0,

@@ -124,9 +124,8 @@ void release_lowp(sem_plan* p) {
   for (int a = 0; a < 3; ++a)
     for (int d = 0; d < 2; ++d) {
       (void)hipFree(p->lp_f32[a][d]);
-      (void)hipFree(p->lp_hi[a][d]);  // lp_lo points into the same allocation
       (void)hipFree(p->lpf[a][d]);
-      p->lp_f32[a][d] = p->lp_hi[a][d] = p->lp_lo[a][d] = p->lpf[a][d] = nullptr;
+      p->lp_f32[a][d] = p->lpf[a][d] = nullptr;
     }
   for (float*& g : p->lps) {
     (void)hipFree(g);
@@ -139,11 +138,10 @@ void release_lowp(sem_plan* p) {
   p->lp_ready = 0;
 }
 
-// Low-precision copies of the factors, layout [l][k] (row l = output mode,
-// contraction k contiguous), zero-padded to pitch ld = pad256(n): FP32 with
-// ld + 96 rows (whole tiles of 128, 96, 64 or 32 rows stay inside), and BF16 hi
-// followed by BF16 lo = bf16(v - hi) with ld rows each in one allocation
-// (lp_lo = lp_hi + ld * ld elements).
+// Low-precision copies of the factors.  Dense FP32, layout [l][k] (row l = output mode,
+// contraction k contiguous), zero-padded to pitch ld = pad256(n) and ld + 96 rows (whole
+// tiles of 128, 96, 64 or 32 rows stay inside); reflection-split BF16 hi and lo =
+// bf16(v - hi); FP32 strips.
 static sem_status ensure_lowp(sem_plan* p) {
   if (p->lp_ready) return SEM_OK;
   for (int a = 0; a < 3; ++a) {
@@ -153,25 +151,14 @@ static sem_status ensure_lowp(sem_plan* p) {
     for (int d = 0; d < 2; ++d) {
       const std::vector<double>& M = d == 0 ? p->ax[a].F : p->ax[a].S;
       std::vector<float> f32(plane + 96 * (size_t)ld, 0.0f);
-      std::vector<unsigned short> hl(2 * plane, 0);
       for (int l = 0; l < n; ++l)
-        for (int k = 0; k < n; ++k) {
-          const double v = M[(size_t)l * n + k];
-          const float fv = (float)v;
-          f32[(size_t)l * ld + k] = fv;
-          const unsigned short h = host_f2bf(fv);
-          hl[(size_t)l * ld + k] = h;
-          hl[plane + (size_t)l * ld + k] = host_f2bf((float)(v - (double)host_bf2f(h)));
-        }
+        for (int k = 0; k < n; ++k) f32[(size_t)l * ld + k] = (float)M[(size_t)l * n + k];
       hipError_t e;
       if ((e = hipMalloc(&p->lp_f32[a][d], f32.size() * 4)) != hipSuccess ||
-          (e = hipMemcpy(p->lp_f32[a][d], f32.data(), f32.size() * 4, hipMemcpyHostToDevice)) != hipSuccess ||
-          (e = hipMalloc(&p->lp_hi[a][d], hl.size() * 2)) != hipSuccess ||
-          (e = hipMemcpy(p->lp_hi[a][d], hl.data(), hl.size() * 2, hipMemcpyHostToDevice)) != hipSuccess) {
+          (e = hipMemcpy(p->lp_f32[a][d], f32.data(), f32.size() * 4, hipMemcpyHostToDevice)) != hipSuccess) {
         release_lowp(p);
         return hip_fail(e, "low-precision factor upload");
       }
-      p->lp_lo[a][d] = (unsigned short*)p->lp_hi[a][d] + plane;
     }
     // reflection-split factors (BF16 hi / lo): forward [modes][representatives],
     // backward [representatives][modes of the block]

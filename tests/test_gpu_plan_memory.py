@@ -9,11 +9,14 @@ MB = 1 << 20
 
 
 def _used(torch, step):
-    torch.cuda.synchronize()
-    before = torch.cuda.mem_get_info()[0]
+    """What step() returns, and the device memory it left allocated outside torch."""
+    def held():
+        torch.cuda.synchronize()
+        free, total = torch.cuda.mem_get_info()
+        return total - free - torch.cuda.memory_reserved()
+    before = held()
     out = step()
-    torch.cuda.synchronize()
-    return out, before - torch.cuda.mem_get_info()[0]
+    return out, held() - before
 
 
 def test_plan_holds_one_copy_of_the_fp64_factors():
@@ -27,3 +30,18 @@ def test_plan_holds_one_copy_of_the_fp64_factors():
     plan, used = _used(torch, lambda: P.Plan(1, (1024, 1024, 1024), (-1, 1) * 3, 1.0, "dirichlet"))
     dense, strips = 2 * 1024 * 1024 * 8, 4 * (512 + 32) * 512 * 8
     assert plan.shape == (1023,) * 3 and 0 < used <= 3 * (dense + strips) + 12 * MB, used / MB
+
+
+def test_low_precision_factors_are_those_that_solves_read():
+    """Two axes of 1023 nodes: dense FP32 (1024 + 96 rows), split-BF16 half-size blocks and
+    FP32 strips; dense BF16 factors, which no kernel reads, would be 8 MiB an axis."""
+    import torch
+    import paper_2310_00226_amd as P
+    small = P.Plan(1, (4, 4, 4), (-1, 1) * 3, 1.0, "dirichlet")
+    small.solve_lowp(torch.ones(small.shape, dtype=torch.float64, device="cuda"), prec="f32")
+    plan = P.Plan(1, (1024, 1024, 4), (-1, 1) * 3, 1.0, "dirichlet")
+    f = torch.ones(plan.shape, dtype=torch.float64, device="cuda")
+    gc.collect()
+    _, used = _used(torch, lambda: plan.solve_lowp(f, prec="f32"))
+    dense, blocks, strips = 2 * 1120 * 1024 * 4, 2 * 2 * 1024 * 512 * 2, 4 * (512 + 32) * 512 * 4
+    assert 0 < used <= 2 * (dense + blocks + strips) + 10 * MB, used / MB
