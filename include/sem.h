@@ -201,9 +201,10 @@ sem_status sem_solve_lowp(sem_plan *p, sem_prec prec, const double *f, double *u
  * which solves run where an axis is longer than 1024 nodes (with shorter axes they
  * run products of fixed shape: a solve tunes nothing, the choices apply to
  * sem_lowp_pass alone); for
- * SEM_BF16 / SEM_BF16X3 the tile order, g = 1, 2 or 4 column strips of 256 that
- * consecutive workgroups share, and the launch: one workgroup per tile (value g)
- * or one workgroup per compute unit looping over the tiles (value 16 + g).  The
+ * SEM_BF16 / SEM_BF16X3 the tile order, g = 1, 2 or 4 column strips of a tile's width
+ * that consecutive workgroups share, and the launch: one workgroup per tile (value g)
+ * or as many workgroups as fit the compute units looping over the tiles (value
+ * 16 + g).  The
  * timed candidates are 1, 4, 17 and 20.  The shapes change no result bit.  Each candidate is launched
  * once untimed, then three times, on the plan's own workspace; the fastest is kept
  * in the plan and in a process-wide cache keyed by device architecture, kernel, block
@@ -319,8 +320,9 @@ sem_status sem_batch_tile_rows(const sem_batch *b, int rows[6]);
  *  SEM_F32: the refinement of sem_solve_refined for every problem at once; each
  *           of the six mode products of an iteration is one persistent launch per
  *           tile shape over all still-unconverged problems of less than 10^6
- *           unknowns, each residual one launch per k and block shape; larger
- *           problems run the products of sem_solve_refined, one launch each, on
+ *           unknowns or with an axis of more than 1024 nodes, each residual one
+ *           launch per k and block shape; the other problems run the products of
+ *           sem_solve_refined, one launch each, on
  *           three side streams that wait on and are joined back into the batch
  *           stream, concurrently with the persistent launches.  One
  *           synchronisation per iteration (norm read-back).

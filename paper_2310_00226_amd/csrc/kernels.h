@@ -153,8 +153,8 @@ enum { LP_F32 = 1, LP_BF16 = 2, LP_BF16X3 = 3 };
 // (non-negative doubles order like their unsigned bits).  Blocks spread their
 // atomic maxima over NORM_SLOTS slots of one 128-byte line each: with one slot for
 // all, the atomics of a launch (device scope, past the XCDs' L2s) queue up at about
-// 12 ns each, which was 89 of the 89 us of the unfold at n = 119 (3600 blocks) and
-// 60 of the 82 us of the last FP32 pass at (127, 163, 143).
+// 12 ns each.  Unfold at n = 119 (3600 blocks) with one slot / these: 89 / 14.5 us; last
+// dense FP32 pass at (127, 163, 143) 82 us with one slot, 21 without norms.
 constexpr int NORM_SLOTS = 32, NORM_STRIDE = 16;       // stride in 8-byte words
 constexpr int NORM_WORDS = NORM_SLOTS * NORM_STRIDE;  // words per solve
 __device__ inline void norm_max(unsigned long long* norms, double dmax, double umax) {
@@ -216,7 +216,7 @@ struct LpPass {
   // tuned launch shapes: FP32 factor-tile rows (128, 96, 64, 32; 0 = by rule);
   // BF16 tile order: groups of g p-strips step through the l-tiles together
   // (g = 1: every l-tile of one p-strip in a row); tile_group = g launches one
-  // block per tile, DMA_PERSIST + g one block per CU looping over the tiles
+  // block per tile, DMA_PERSIST + g as many blocks as fit the CUs looping over the tiles
   int tile_rows = 0;
   int tile_group = 1;
 };

@@ -847,8 +847,8 @@ static hipError_t launch_dma_g(const LpPass& ps, hipStream_t stream) {
   g.epi = ps.epi;
   dma_tiles<G>(ps, &g.tl1, &g.tiles_l, &g.tiles_p);
   g.ntiles = g.tiles_l * g.tiles_p;
-  // tile_group: g in {1, 2, 4} (one block per tile) or DMA_PERSIST + g (one block
-  // per CU looping over the tiles)
+  // tile_group: g in {1, 2, 4} (one block per tile) or DMA_PERSIST + g (as many blocks
+  // as fit the CUs looping over the tiles)
   const int tg = ps.tile_group >= 1 ? ps.tile_group : 1;
   g.persist = tg > DMA_PERSIST ? 1 : 0;
   g.group = g.persist ? tg - DMA_PERSIST : tg;

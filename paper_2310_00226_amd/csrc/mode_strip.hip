@@ -160,10 +160,10 @@ __device__ __forceinline__ float multiply(float v, double lam, const EpiArgs& e)
 // all 64 banks, every second one swaps its 16-column halves, so that they do not meet.
 template <class T, int W>
 __device__ __forceinline__ int at(int m, int c) {
+  static_assert(W == 16 || W == 32, "one or two column tiles");
   constexpr int SPAN = W * (int)sizeof(T) / 128;  // 1: two rows span the banks
   if constexpr (sizeof(T) == 8 && SPAN >= 2) return m * W + (c ^ ((m & 1) << 4));
   else if constexpr (sizeof(T) == 4 && SPAN == 1) return m * W + (c ^ (((m ^ (m >> 1)) & 1) << 4));
-  else if constexpr (sizeof(T) == 4 && SPAN >= 2) return m * W + (c ^ ((m & 3) << 4));
   else return m * W + c;
 }
 

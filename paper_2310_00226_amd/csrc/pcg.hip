@@ -142,7 +142,7 @@ template <int NS>
 __global__ __launch_bounds__(DOT_THREADS) void pcg_update_fold(double* __restrict__ u, double* __restrict__ r,
                                                                const double* __restrict__ p,
                                                                const double* __restrict__ q,
-                                                          const double* __restrict__ scal,
+                                                               const double* __restrict__ scal,
                                                                const double* __restrict__ mx,
                                                                const double* __restrict__ my,
                                                                const double* __restrict__ mz, int nx, int ny, int nz,

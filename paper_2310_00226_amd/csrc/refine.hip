@@ -400,7 +400,7 @@ bool f64_strip(const sem_plan* p, int a) {
 bool f32_strips(const sem_plan* p) {
   for (int a = 0; a < 3; ++a)
     if (!strip_axis_ok(strip_axis(p, a), sizeof(float))) return false;
-  return (long)p->dims[1] * p->dims[2] <= STRIP_MAX_Q;
+  return true;  // such planes are far below STRIP_MAX_Q
 }
 
 // The FP32 FD application on strips: src -> t0 (z), in place (y, x, y), t0 -> u.  Half
@@ -538,8 +538,8 @@ hipError_t lp_fd(sem_plan* p, const LpWork& w, const Spectral& sp, const double*
 
 // ---- autotuning of the launch shapes -------------------------------------------
 // FP32 passes: factor-tile rows 128, 96, 64 or 32; BF16 passes: tile order group
-// of 1 or 4 p-strips, with one block per tile or one block per CU looping over
-// the tiles (DMA_PERSIST + group).  Each pass geometry is timed once (one warm-up launch, the
+// of 1 or 4 p-strips, with one block per tile or as many blocks as fit the CUs looping
+// over the tiles (DMA_PERSIST + group).  Each pass geometry is timed once (one warm-up launch, the
 // fastest of three), on the plan's own workspace, and the choice is kept in the
 // plan and in the tuning cache (key: architecture, kernel with its block tile, output
 // layout, and log2 buckets of rows, contraction length and tensor rows), so plans of similar
