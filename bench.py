@@ -326,7 +326,7 @@ def bench_ch(args, P, torch, dev, log):
            "max_abs_phi": float(np.max(np.abs(phi))),
            "roofline": {"bound": "mfma", "kernel": "whole step (FD application counted: 4 N (nx+ny+nz) flop)",
                         "achieved": ach, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_FP32_TFLOPS},
-           "tuned_shapes": ch.tuning()}
+           "tuned_shapes": None}  # FP32 strips: no shape to tune
     if args.ch_oracle_steps > 0 and not args.no_cpu_baseline:
         import oracle as O
         # the same start, args.ch_oracle_steps steps on the GPU and in the oracle
@@ -445,8 +445,8 @@ def main() -> int:
             variants[f"{prec}_refined"] = {"ms_per_solve": vms, "unknowns_per_s": N / (vms * 1e-3),
                                            "iterations": it, "last_update_rel": rel, "status": st,
                                            "rel_err_vs_f64": err,
-                                           # launch shapes the first solve tuned, per pass in order:
-                                           # FP32 tile rows / BF16 tile-order group
+                                           # launch shapes the first solve tuned, per pass in order
+                                           # (BF16 tile-order group; FP32 strips have none)
                                            "tuned_shapes": plan.tuning(prec)}
             log(f"{prec} refined: {vms:.2f} ms/solve, {N / (vms * 1e-3):.3e} unknowns/s, {it} iterations, "
                 f"rel err vs FP64 {err:.2e}, status {st}")
